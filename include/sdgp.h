@@ -165,18 +165,19 @@ sdgp_status sdgp_set_timing(sdgp_ctx* ctx, int enable);
  * until every column (and every population member) has converged; the
  * iteration counters live on the device, so replays past convergence or
  * past cg_max_iter do nothing; "union_spmm" (-1 default: on from
- * 65536 points when the lists fit in half of the free device memory, 0 off,
- * 1 on): the
- * CG SpMM reads, for every 4 consecutive rows of its row order, one sorted
- * list of the 4 rows' distinct columns with 4 values per entry (0 where a
- * row lacks the column), so each neighbour row of P is gathered once for
- * the 4 rows (lists built once per solve); "fw_mfma" (-1 default = 1, 0, 1):
+ * 65536 points when the lists fit in half of the free device memory and in
+ * the context's "workspace_cap", 0 off, 1 on): the
+ * CG SpMM reads, for every 16 consecutive rows of its row order, one sorted
+ * list of the 16 rows' distinct columns and their values in that order, so
+ * each neighbour row of P is gathered once for the 16 rows and the products
+ * run on the matrix cores (lists built once per solve); "fw_mfma" (-1 default = 1, 0, 1):
  * the preconditioner / factored-operator products
  * F w of the CG update kernels per 16-row tile on the matrix cores instead
  * of per-row broadcasts; "update_blocks" (0 default: one round of the
  * blocks the GPU holds at once, from the kernels' occupancy; or 1..65535):
  * the grid size of the CG update kernels (at most one block per 16 rows);
- * "spmm_blocks" (0 default = 32768, or a multiple of 8 up to 65535): the
+ * "spmm_blocks" (0 default: one resident round over the union lists, 32768
+ * over CSR rows; or a multiple of 8 up to 65535): the
  * grid size of the CG SpMM (blocks are dealt to the 8 XCDs in turn).
  * "autotune" (0 off, 1 default, 2): the CG launch-shape autotuner.  The
  * first solve of a problem class (device architecture, bump-function count

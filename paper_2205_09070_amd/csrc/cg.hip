@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -37,12 +38,18 @@ namespace {
 
 constexpr int kT = 256;          // threads per block
 constexpr int kTile = 16;        // rows per block tile (4 waves x 4 groups of 16 lanes)
+constexpr int kGR = 16;          // rows per group of the union lists (one wavefront's)
+constexpr int kUTile = 4 * kGR;  // rows per block step of the union-list SpMM
+constexpr int kBE = 64;          // list columns per batch of the union-list SpMM (one per lane)
+constexpr int kBS = 6;           // its logarithm
+constexpr int kUnionPerCu = 4;   // resident blocks of the union-list SpMM per CU (its launch bounds)
 constexpr int kSlab = 32;        // columns per slab
 constexpr int kSC = kSlab + 1;   // LDS stride of per-column values (slab columns + column 0)
 constexpr int kMaxNbs = 32768;   // SpMM blocks
 constexpr int kMaxNbu = 8192;    // upper bound on the update kernels' grid (default: one resident round)
 constexpr int kGS = 2;           // row-steps whose loads the update passes issue together
 constexpr int64_t kUnionMinRows = 65536;  // union-list SpMM by default from this many rows
+constexpr int64_t kUnionCheckRows = (int64_t)1 << 25;  // from here 16 rows could hold 2^29 entries
 
 struct CgState {
   double* rz;       // [2][R] parity buffers of r.z (r.r unpreconditioned)
@@ -84,13 +91,19 @@ struct CgArgs {
   double* w_red;              // [(n1+1) R]: u = S^{-1} g (row i R + c), then g.u (row n1 R + c)
   double* p_part;             // [n1 R][nbu] F^T p (row i R + c)
   double* p_red;              // [n1 R]
-  // 4-row union lists of the shared-gather SpMM: group q = schedule rows
-  // 4q .. 4q+3; entries urp[q] .. urp[q+1]-1 hold the group's distinct
-  // columns (ascending, ucol) and their 4 values (uval[4e + r] for row 4q+r,
-  // 0 where that row lacks the column)
-  const int64_t* urp;
+  // Union lists of the shared-gather SpMM: group q = schedule rows 16q ..
+  // 16q+15, its storage gv[q] .. gv[q+1]-1 (as many places as the rows have
+  // entries).  ucol[gv[q] + e], e < glen[q]: the group's distinct columns,
+  // ascending.  uval / upos[gv[q] + i]: every stored value in (column, row)
+  // order with its place in the 64 x 16 tile of its batch of 64 columns; the
+  // values of batch b start at gb[gv[q]/64 + q + b] (relative to gv[q]).
+  const int64_t* gv;
+  const int32_t* glen;
+  const uint32_t* gend;       // end of the group's values (relative to gv[q])
+  const uint32_t* gb;
   const int32_t* ucol;
   const double* uval;
+  const uint16_t* upos;
   CgState st;
 };
 
@@ -306,206 +319,322 @@ __global__ __launch_bounds__(kT) void k_cg_spmm(const CgArgs* __restrict__ AA) {
 }
 
 // ------------------------------------------------------- union-list SpMM
-// Lists of the shared-gather SpMM, built once per solve.  A group is four
-// consecutive rows of the row schedule (the four rows one wavefront of the
-// SpMM owns); its list is the merge of the four rows' ascending column lists.
-// One thread per group; k_union_count writes the list lengths, k_union_fill
-// (after a scan into urp) the columns and values.
-__device__ __forceinline__ void union_head(int64_t n, int64_t p, const int64_t* __restrict__ rp,
-                                           const int32_t* __restrict__ sched, int64_t& k, int64_t& e) {
-  k = e = 0;
-  if (p < n) {
+// Lists of the shared-gather SpMM, built once per solve: a group is 16
+// consecutive rows of the row schedule (one wavefront of the SpMM).
+// Entries per group (the storage each group's lists take).
+__global__ __launch_bounds__(256) void k_group_nnz(int64_t n, int64_t ng, const int64_t* __restrict__ rp,
+                                                   const int32_t* __restrict__ sched, int64_t* __restrict__ cnt) {
+  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (q > ng) return;
+  int64_t s = 0;
+  for (int64_t p = q * kGR; p < min(n, (q + 1) * kGR); ++p) {
+    const int64_t a = sched ? (int64_t)sched[p] : p;
+    s += rp[a + 1] - rp[a];
+  }
+  // whole multiples of 4 with room for every batch to begin at one
+  cnt[q] = q < ng ? (s + 3 * (s / kBE + 1) + 3) & ~(int64_t)3 : 0;
+}
+
+// One wavefront per group merges the 16 rows' ascending column lists in
+// windows: every row's next 64 entries up to the smallest 64th column go into
+// LDS as keys (column, row, place), four rounds of pairwise merges (each key's
+// rank from a binary search in the partner list) sort them, and the sorted
+// keys are written out with a running count of distinct columns.
+constexpr int kGBW = 2;                         // wavefronts per block (16 KiB of LDS each)
+__global__ __launch_bounds__(kGBW * kWave) void k_group_lists(
+    int64_t n, int64_t ng, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+    const double* __restrict__ val, const int32_t* __restrict__ sched, const int64_t* __restrict__ gv,
+    int32_t* __restrict__ glen, uint32_t* __restrict__ gend, uint32_t* __restrict__ gb, int32_t* __restrict__ ucol, double* __restrict__ uval,
+    uint16_t* __restrict__ upos) {
+  __shared__ uint64_t buf[kGBW][2][kGR * kWave];
+  __shared__ int64_t heads[kGBW][kGR];
+  const int lane = lane_id(), w = threadIdx.x >> 6;
+  const int64_t q = (int64_t)blockIdx.x * kGBW + w;
+  if (q >= ng) return;                          // whole wavefronts; no block barrier below
+  int64_t k = 0, e = 0;                         // lane r < 16: row r's next entry and its end
+  if (lane < kGR && q * kGR + lane < n) {
+    const int64_t p = q * kGR + lane;
     const int64_t a = sched ? (int64_t)sched[p] : p;
     k = rp[a];
     e = rp[a + 1];
   }
-}
-__device__ __forceinline__ int32_t head_col(int64_t k, int64_t e, const int32_t* __restrict__ col) {
-  return k < e ? col[k] : INT32_MAX;
-}
-__global__ __launch_bounds__(256) void k_union_count(int64_t n, int64_t ng, const int64_t* __restrict__ rp,
-                                                     const int32_t* __restrict__ col,
-                                                     const int32_t* __restrict__ sched, int32_t* __restrict__ cnt) {
-  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (q >= ng) return;
-  int64_t k0, e0, k1, e1, k2, e2, k3, e3;
-  union_head(n, 4 * q, rp, sched, k0, e0);
-  union_head(n, 4 * q + 1, rp, sched, k1, e1);
-  union_head(n, 4 * q + 2, rp, sched, k2, e2);
-  union_head(n, 4 * q + 3, rp, sched, k3, e3);
-  int32_t c = 0;
-  for (;;) {
-    const int32_t h0 = head_col(k0, e0, col), h1 = head_col(k1, e1, col);
-    const int32_t h2 = head_col(k2, e2, col), h3 = head_col(k3, e3, col);
-    const int32_t m = min(min(h0, h1), min(h2, h3));
-    if (m == INT32_MAX) break;
-    k0 += h0 == m;
-    k1 += h1 == m;
-    k2 += h2 == m;
-    k3 += h3 == m;
-    ++c;
+  const int64_t v0 = gv[q], slot = (v0 >> kBS) + q;
+  int ecount = 0;                               // distinct columns so far (uniform)
+  uint32_t vcount = 0;                          // values so far (uniform)
+  while (__any(k < e)) {
+    int32_t cut = e - k > kWave ? col[k + kWave - 1] : INT32_MAX;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) cut = min(cut, __shfl_xor(cut, o, 64));
+    if (lane < kGR) heads[w][lane] = k;
+    int T = 0, taken = 0;
+    for (int r = 0; r < kGR; ++r) {
+      const int64_t t = (int64_t)readlane_u64((uint64_t)k, r) + lane;
+      const bool in = t < (int64_t)readlane_u64((uint64_t)e, r);
+      const int32_t c = in ? col[t] : INT32_MAX;
+      const bool take = in && c <= cut;
+      buf[w][0][r * kWave + lane] = take ? (uint64_t)(uint32_t)c << 10 | (uint64_t)(r << 6 | lane) : ~0ull;
+      const int m = __popcll(ballot64(take));
+      if (lane == r) taken = m;
+      T += m;
+    }
+    const uint64_t* src = buf[w][0];
+    uint64_t* dst = buf[w][1];
+    for (int len = kWave; len < kGR * kWave; len <<= 1) {
+      __builtin_amdgcn_wave_barrier();
+      for (int x = lane; x < kGR * kWave; x += kWave) {
+        const int base = x & ~(2 * len - 1), in = x - base;
+        const bool hi = in >= len;
+        const uint64_t key = src[x];
+        const uint64_t* other = src + base + (hi ? 0 : len);
+        int l = 0, h = len;                     // partner keys before this one (equal ones: padding only)
+        while (l < h) {
+          const int mid = (l + h) >> 1;
+          const uint64_t v = other[mid];
+          if (v < key || (hi && v == key)) l = mid + 1; else h = mid;
+        }
+        dst[base + (hi ? in - len : in) + l] = key;
+      }
+      const uint64_t* tmp = src;
+      src = dst;
+      dst = const_cast<uint64_t*>(tmp);
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int i0 = 0; i0 < T; i0 += kWave) {
+      const int i = i0 + lane;
+      const uint64_t key = i < T ? src[i] : ~0ull;
+      const bool first = i < T && (i == 0 || (src[i - 1] >> 10) != (key >> 10));
+      const uint64_t bal = ballot64(first);
+      const int ei = ecount + lanes_below(bal) + (first ? 1 : 0) - 1;   // the value's column in the list
+      // a batch's values begin at a multiple of 4: lanes from a batch's first
+      // value on move up
+      const uint64_t open = ballot64(first && (ei & (kBE - 1)) == 0);
+      uint32_t o = vcount + lane;                 // next free place (uniform part) plus the lane
+      for (uint64_t m = open; m; m &= m - 1) {
+        const int l0 = __builtin_ctzll(m);
+        const uint32_t at = (uint32_t)readlane_i32((int)o, l0), up = (4 - (at & 3)) & 3;
+        if (lane == l0)
+          for (uint32_t t = at; t < at + up; ++t) {   // unused places: a value for the place past the tile
+            uval[v0 + t] = 0.0;
+            upos[v0 + t] = (uint16_t)(kBE * kGR);
+          }
+        if (lane >= l0) o += up;
+      }
+      const int nvl = min(kWave, T - i0);
+      if (i < T) {
+        const int r = (int)(key >> 6) & (kGR - 1);
+        uval[v0 + o] = val[heads[w][r] + (int64_t)(key & 63)];
+        upos[v0 + o] = (uint16_t)((ei & (kBE - 1)) * kGR + (r & 3) * 4 + (r >> 2));
+        if (first) {
+          ucol[v0 + ei] = (int32_t)(key >> 10);
+          if ((ei & (kBE - 1)) == 0) gb[slot + (ei >> kBS)] = o;
+        }
+      }
+      vcount = (uint32_t)readlane_i32((int)o, nvl - 1) + 1;
+      ecount += __popcll(bal);
+    }
+    k += taken;
+    __builtin_amdgcn_wave_barrier();            // the window's keys and heads are read
   }
-  cnt[q] = c;
-}
-__global__ __launch_bounds__(256) void k_union_fill(int64_t n, int64_t ng, const int64_t* __restrict__ rp,
-                                                    const int32_t* __restrict__ col, const double* __restrict__ val,
-                                                    const int32_t* __restrict__ sched, const int64_t* __restrict__ urp,
-                                                    int32_t* __restrict__ ucol, double* __restrict__ uval) {
-  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (q >= ng) return;
-  int64_t k0, e0, k1, e1, k2, e2, k3, e3;
-  union_head(n, 4 * q, rp, sched, k0, e0);
-  union_head(n, 4 * q + 1, rp, sched, k1, e1);
-  union_head(n, 4 * q + 2, rp, sched, k2, e2);
-  union_head(n, 4 * q + 3, rp, sched, k3, e3);
-  const int64_t u0 = urp[q], u1 = urp[q + 1];
-  for (int64_t u = u0; u < u1; ++u) {   // the merge yields exactly u1 - u0 entries (k_union_count)
-    const int32_t h0 = head_col(k0, e0, col), h1 = head_col(k1, e1, col);
-    const int32_t h2 = head_col(k2, e2, col), h3 = head_col(k3, e3, col);
-    const int32_t m = min(min(h0, h1), min(h2, h3));
-    if (m == INT32_MAX) break;
-    ucol[u] = m;
-    uval[4 * u + 0] = h0 == m ? val[k0++] : 0.0;
-    uval[4 * u + 1] = h1 == m ? val[k1++] : 0.0;
-    uval[4 * u + 2] = h2 == m ? val[k2++] : 0.0;
-    uval[4 * u + 3] = h3 == m ? val[k3++] : 0.0;
+  if (lane == 0) {
+    glen[q] = ecount;
+    gend[q] = vcount;
   }
 }
 
-// One union entry for all four rows: the entry's gathered slab row (lane j:
-// columns 2j, 2j+1), times each row's value (row-broadcast from the lane
-// holding the entry), is added into the four rows' accumulators.
-template <int u>
-__device__ __forceinline__ void union_fma(const dv2& x, const double* vr, double (*acc)[2]) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const double v = bcast16_d<u>(vr[r]);
-    acc[r][0] += v * x.x;
-    acc[r][1] += v * x.y;
-  }
+// A value that is the same in every lane of the wavefront, in scalar registers.
+__device__ __forceinline__ int64_t uniform_i64(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+  return (int64_t)((uint64_t)hi << 32 | lo);
 }
-template <int... us>
-__device__ __forceinline__ void union_batch(int cj, const double* vr, const GL double* __restrict__ Xs,
-                                            double (*acc)[2], std::integer_sequence<int, us...>) {
-  // all 16 gathers in flight before the arithmetic
-  dv2 xv[16];
-  ((xv[us] = *reinterpret_cast<const GL dv2*>(Xs + (int64_t)(uint32_t)bcast16_i<us>(cj) * kSlab)), ...);
-  ((union_fma<us>(xv[us], vr, acc)), ...);
+
+// Gathers of steps 4c .. 4c+3 of a batch: step u takes the entry held by lane
+// u of each 16-lane group (off: byte offset of the entry's slab row, or the
+// row itself when kWide), the lane's two slab columns of it.
+template <bool kWide, int c, int... us>
+__device__ __forceinline__ void union_load(uint32_t off, const GL char* __restrict__ Pb, uint32_t lj, dv2* xv,
+                                           std::integer_sequence<int, us...>) {
+  if constexpr (kWide)
+    ((xv[4 * c + us] = *reinterpret_cast<const GL dv2*>(Pb + (int64_t)(uint32_t)bcast16_i<4 * c + us>((int)off) *
+                                                                 (kSlab * 8) + lj)), ...);
+  else
+    ((xv[4 * c + us] = *reinterpret_cast<const GL dv2*>(Pb + ((uint32_t)bcast16_i<4 * c + us>((int)off) + lj))), ...);
+}
+
+// Products of steps 4c .. 4c+3 on the FP64 matrix cores.
+// v_mfma_f64_4x4x4_4b adds four independent 4 x 4 x 4 products; lane
+// 16 k + 4 b + x holds A_b[x][k], B_b[k][x] and D_b[k][x] (checked on gfx950).
+// With four of the group's rows as the rows of A, the four entries of a step
+// (one per 16-lane group) as K and the slab's columns over (b, x), the even
+// and odd columns of the lane's gather are B as they arrive, and lane (g, j)
+// ends with columns 2j, 2j+1 of row 4R + g in acc[R]: nothing is summed across
+// lanes.  Column 0: B is the entry's y in every lane of its group and b selects
+// the row quad, so lane 16 i + 4 b + x ends with row 4b + i.  at: the lane's
+// values of the chunk's first entry in the tile, R = 0..3.  (One value per
+// lane with the row quads rotated round the blocks by DPP measured 0.233 ms
+// against 0.188 at 400,000 points: the rotations stand between the tile's
+// loads and the products.)  The 4 x 4 x 4 form runs at 73 TFLOP/s on this
+// card, the 16 x 16 x 4 form at 48.
+template <bool kY, int c, int... us>
+__device__ __forceinline__ void union_mma(const dv2* xv, double yv, const double* at, const double* aty,
+                                          double (&acc)[4][2], double& accy, std::integer_sequence<int, us...>) {
+  auto step = [&](int u, const dv2& x, double yb) {   // u: the step's place in the list for group 0
+    const dv2 a01 = *reinterpret_cast<const dv2*>(at + kGR * u),
+              a23 = *reinterpret_cast<const dv2*>(at + kGR * u + 2);
+    acc[0][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a01.x, x.x, acc[0][0], 0, 0, 0);
+    acc[0][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a01.x, x.y, acc[0][1], 0, 0, 0);
+    acc[1][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a01.y, x.x, acc[1][0], 0, 0, 0);
+    acc[1][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a01.y, x.y, acc[1][1], 0, 0, 0);
+    acc[2][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a23.x, x.x, acc[2][0], 0, 0, 0);
+    acc[2][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a23.x, x.y, acc[2][1], 0, 0, 0);
+    acc[3][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a23.y, x.x, acc[3][0], 0, 0, 0);
+    acc[3][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a23.y, x.y, acc[3][1], 0, 0, 0);
+    if constexpr (kY) accy = __builtin_amdgcn_mfma_f64_4x4x4f64(aty[kGR * u], yb, accy, 0, 0, 0);
+  };
+  ((step(16 * c + us, xv[4 * c + us], kY ? bcast16_d<4 * c + us>(yv) : 0.0)), ...);
 }
 
 // Q = A P over the union lists, per-block partials of p.q as in k_cg_spmm.
-// A wavefront owns the four rows of one group and walks the group's list 64
-// entries at a time (one entry per lane); each 16-lane group takes 16 of
-// them (row-broadcast of the entry's column and four values), so every
-// listed neighbour row is gathered once for the four rows.  The four groups'
-// partial sums are then added across the wavefront.  kMode 1: slab 0 and
+// A wavefront owns the 16 rows of one group and walks the group's list 64
+// columns at a time: the batch's stored values are scattered into a zeroed
+// 64 x 16 tile in LDS, every listed neighbour row is gathered once for the 16
+// rows (16 lanes x 16 bytes), and the products run on the matrix cores.
+// Why 16 rows and compact values: the kernel's time followed the bytes through
+// each CU's gather path (4-row lists 27.7 gathered rows per row at ~60 entries
+// per row in 3-D, 16-row lists 13.6) and the lists stream from HBM (4-row
+// lists with a dense 4-value entry 1.0 KB per row, these 0.65 KB).  Per launch
+// with 33 columns, factored operator: 0.293 -> 0.180 ms at 400,000 points in
+// 3-D (60 entries per row), 0.695 -> 0.470 ms at 1,000,000 points in 4-D (50);
+// matrix cores 44% busy, LDS 25%, the texture data path 87%.  Measured and not
+// kept (ms at 400,000 points): the next batch's columns loaded a batch ahead
+// 0.196 against 0.188; batches of 32 columns at 4 / 5 / 6 wavefronts per SIMD
+// 0.203 / 0.202 / 0.215 against 0.185; values loaded one by one 0.188.
+// kWide: slabs of 4 GiB and more (64-bit row offsets).  kMode 1: slab 0 and
 // column 0 (grid y = 1); kMode 2: slabs 1.. (grid y = ns - 1).  Groups are
 // dealt to the XCDs in contiguous runs (the XCD share rounded to whole
-// groups); each wavefront loads the list bounds of its next group while it
-// works on the current one.
-template <int kMode>
-__global__ __launch_bounds__(kT) void k_cg_spmm_u(const CgArgs* __restrict__ AA) {
+// groups).
+template <int kMode, bool kWide>
+__global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __restrict__ AA) {
   const CgArgs& A = AA[blockIdx.z];
   const Gv G = gview(A);
   if (stopped(A)) return;
   constexpr bool kY = kMode == 1;
-  __shared__ double red[kTile * kSlab];
-  __shared__ double redy[kTile];
-  const GL int64_t* urp = (const GL int64_t*)A.urp;
+  constexpr int kVL = 3;                          // values per lane loaded ahead (384 of a batch's at most 1024)
+  __shared__ __align__(16) double tile[kT / kWave][kBE * kGR + 2];   // (+ the unused places' target)
+  const GL int64_t* gv = (const GL int64_t*)A.gv;
+  const GL int32_t* glen = (const GL int32_t*)A.glen;
+  const GL uint32_t* gend = (const GL uint32_t*)A.gend;
+  const GL uint32_t* gb = (const GL uint32_t*)A.gb;
   const GL int32_t* ucol = (const GL int32_t*)A.ucol;
-  const GL dv2* uval = (const GL dv2*)A.uval;
-  const int lane = lane_id(), g = lane >> 4, j = lane & 15, w = threadIdx.x >> 6;
+  const GL double* uval = (const GL double*)A.uval;
+  const GL uint16_t* upos = (const GL uint16_t*)A.upos;
+  const int lane = lane_id(), g = lane >> 4, j = lane & 15, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int s = kMode == 2 ? (int)blockIdx.y + 1 : 0;
   const int64_t n = A.n;
   const int64_t so = A.ny + (int64_t)s * n * kSlab + 2 * j;
   const GL double* Ps = G.P + so;
   GL double* Qs = G.Q + so;
+  const GL char* Pb = (const GL char*)(G.P + (A.ny + (int64_t)s * n * kSlab));
+  double* tw = tile[w];
+  const double* at = tw + 4 * g * kGR + (lane & 3) * 4;
+  const double* aty = at + ((lane >> 2) & 3);
   const int xcd = blockIdx.x & 7;
   const int64_t bi = blockIdx.x >> 3, nbx = gridDim.x >> 3;
-  const int64_t nx = (((n + 7) >> 3) + 3) & ~(int64_t)3, lo = xcd * nx, hi = min(n, lo + nx);
+  const int64_t nx = (((n + 7) >> 3) + kGR - 1) & ~(int64_t)(kGR - 1), lo = xcd * nx, hi = min(n, lo + nx);
+  const auto seq = std::make_integer_sequence<int, 4>{};
   double pq0 = 0.0, pq1 = 0.0, pqy = 0.0;
-  const int64_t stride = nbx * kTile;
-  int64_t pb = lo + bi * kTile + w * 4;
-  // list bounds of the current group, those of the next one loaded a group ahead
-  int64_t k0 = 0, k1 = 0;
-  if (pb < hi) {
-    k0 = urp[pb >> 2];
-    k1 = urp[(pb >> 2) + 1];
-  }
-  for (; pb < hi; pb += stride) {
-    const int64_t pn = pb + stride;
-    int64_t k0n = 0, k1n = 0;
-    if (pn < hi) {
-      k0n = urp[pn >> 2];
-      k1n = urp[(pn >> 2) + 1];
-    }
-    const int64_t p = pb + g;
-    const bool live = p < hi;
-    const int64_t a = live ? (G.sched ? (int64_t)G.sched[p] : p) : 0;
-    const int32_t a0 = G.sched ? G.sched[pb] : (int32_t)pb;
+  for (int64_t pb = lo + bi * kUTile + w * kGR; pb < hi; pb += nbx * kUTile) {
+    const int64_t q = pb >> 4;
+    const int64_t v0 = uniform_i64(gv[q]);
+    const uint32_t nv = (uint32_t)__builtin_amdgcn_readfirstlane((int)gend[q]);
+    const int len = __builtin_amdgcn_readfirstlane(glen[q]);
+    const GL uint32_t* gbq = gb + ((v0 >> kBS) + q);
+    const GL char *cb = (const GL char*)(ucol + v0), *vlb = (const GL char*)(uval + v0), *pob = (const GL char*)(upos + v0);
+    const uint32_t a0 = (uint32_t)(G.sched ? G.sched[pb] : (int32_t)pb);
     double acc[4][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-    double ya[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t kb = k0; kb < k1; kb += 64) {     // uniform over the wavefront
-      const int64_t k = kb + lane;
-      const bool in = k < k1;
-      const int cj = in ? ucol[k] : a0;
-      double vr[4] = {0.0, 0.0, 0.0, 0.0};
-      if (in) {
-        const dv2 v01 = uval[2 * k], v23 = uval[2 * k + 1];
-        vr[0] = v01.x;
-        vr[1] = v01.y;
-        vr[2] = v23.x;
-        vr[3] = v23.y;
-      }
-      if (kY) {
-        const double yv = G.P[cj];
+    double accy = 0.0;
+    uint32_t vb = 0;
+    for (int e0 = 0; e0 < len; e0 += kBE) {       // uniform over the wavefront
+      const int rem = len - e0;
+      // the batch ends where the next one begins (up to 3 unused places before it,
+      // whose target lies past the tile)
+      const uint32_t ve = rem > kBE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)gbq[(e0 >> kBS) + 1]) : nv;
+      const int ei = 16 * (j >> 2) + 4 * g + (j & 3);   // step u = 4c + r of group g: entry 16c + 4g + r
+      const uint32_t cj = ei < min(rem, kBE) ? *(const GL uint32_t*)(cb + (uint32_t)(e0 + ei) * 4u) : a0;
+      dv2 vv[kVL];
+      uint32_t pp[kVL];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ya[r] += vr[r] * yv;
+      for (int m = 0; m < kVL; ++m) {             // pairs of values (aligned: batches begin at multiples of 4)
+        const uint32_t i = vb + 2 * (lane + kWave * m);
+        vv[m] = dv2{0.0, 0.0};
+        pp[m] = 0u;
+        if (i < ve) {
+          vv[m] = *(const GL dv2*)(vlb + i * 8u);
+          pp[m] = *(const GL uint32_t*)(pob + i * 2u);
+        }
       }
-      union_batch(cj, vr, Ps, acc, std::make_integer_sequence<int, 16>{});
-    }
-    // the four 16-lane groups' partial sums (lanes j, j+16, j+32, j+48)
+      const double yv = kY ? G.P[cj] : 0.0;
+      const uint32_t off = kWide ? cj : cj * (kSlab * 8);
+      const int nc = (min(rem, kBE) + 15) >> 4;    // steps in fours
+      dv2 xv[kBE / 4];
+      union_load<kWide, 0>(off, Pb, (uint32_t)(16 * j), xv, seq);
+      if (nc > 1) union_load<kWide, 1>(off, Pb, (uint32_t)(16 * j), xv, seq);
+      if (nc > 2) union_load<kWide, 2>(off, Pb, (uint32_t)(16 * j), xv, seq);
+      __builtin_amdgcn_wave_barrier();            // the last batch's tile is read
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      acc[r][0] += __shfl_xor(acc[r][0], 16);
-      acc[r][1] += __shfl_xor(acc[r][1], 16);
-      acc[r][0] += __shfl_xor(acc[r][0], 32);
-      acc[r][1] += __shfl_xor(acc[r][1], 32);
-      if (kY)
-        for (int o = 32; o > 0; o >>= 1) ya[r] += __shfl_xor(ya[r], o);
+      for (int m = 0; m < kBE / 8; ++m) *reinterpret_cast<dv2*>(tw + 2 * (lane + kWave * m)) = dv2{0.0, 0.0};
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int m = 0; m < kVL; ++m) {
+        const uint32_t i = vb + 2 * (lane + kWave * m);
+        if (i < ve) tw[pp[m] & 0xffff] = vv[m].x;
+        if (i + 1 < ve) tw[pp[m] >> 16] = vv[m].y;
+      }
+      for (uint32_t i = vb + 2 * kWave * kVL + lane; i < ve; i += kWave)
+        tw[*(const GL uint16_t*)(pob + i * 2u)] = *(const GL double*)(vlb + i * 8u);
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_s_setprio(1);              // a wavefront with its operands at hand goes first
+      union_mma<kY, 0>(xv, yv, at, aty, acc, accy, seq);
+      if (nc > 3) union_load<kWide, 3>(off, Pb, (uint32_t)(16 * j), xv, seq);
+      if (nc > 1) union_mma<kY, 1>(xv, yv, at, aty, acc, accy, seq);
+      if (nc > 2) union_mma<kY, 2>(xv, yv, at, aty, acc, accy, seq);
+      if (nc > 3) union_mma<kY, 3>(xv, yv, at, aty, acc, accy, seq);
+      __builtin_amdgcn_s_setprio(0);
+      vb = ve;
     }
-    dv2 qv = {acc[0][0], acc[0][1]};
-    double yacc = ya[0];
-    if (g == 1) { qv = dv2{acc[1][0], acc[1][1]}; yacc = ya[1]; }
-    if (g == 2) { qv = dv2{acc[2][0], acc[2][1]}; yacc = ya[2]; }
-    if (g == 3) { qv = dv2{acc[3][0], acc[3][1]}; yacc = ya[3]; }
-    if (live) {
-      st_s(Qs + a * kSlab, qv);
-      const dv2 pv = *reinterpret_cast<const GL dv2*>(Ps + a * kSlab);
-      pq0 += pv.x * qv.x;
-      pq1 += pv.y * qv.y;
-      if (kY && j == 0) {
-        G.Q[a] = yacc;
-        pqy += G.P[a] * yacc;
+#pragma unroll
+    for (int R = 0; R < 4; ++R) {
+      const int64_t p = pb + 4 * R + g;
+      if (p < hi) {
+        const int64_t a = G.sched ? (int64_t)G.sched[p] : p;
+        const dv2 qv = {acc[R][0], acc[R][1]};
+        st_s(Qs + a * kSlab, qv);
+        const dv2 pv = *reinterpret_cast<const GL dv2*>(Ps + a * kSlab);
+        pq0 += pv.x * qv.x;
+        pq1 += pv.y * qv.y;
       }
     }
-    k0 = k0n;
-    k1 = k1n;
+    if (kY && (lane & 3) == 0) {
+      const int64_t p = pb + (lane & 12) + g;     // row 4b + i of lane 16 i + 4 b
+      if (p < hi) {
+        const int64_t a = G.sched ? (int64_t)G.sched[p] : p;
+        G.Q[a] = accy;
+        pqy += G.P[a] * accy;
+      }
+    }
   }
+  double* red = tile[0];
   const double t = tile_colsum(red, pq0, pq1);
   if (threadIdx.x < kSlab) {
     const int rc = 1 + s * kSlab + threadIdx.x;
     if (rc < A.R) G.s_part[(int64_t)rc * A.nbs + blockIdx.x] = t;
   }
   if (kY) {
+    const double ty = wave_sum(pqy);
+    __syncthreads();                              // the slab columns' sums are read
+    if (lane == 0) red[w] = ty;
     __syncthreads();
-    if (j == 0) redy[w * 4 + g] = pqy;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double ty = 0.0;
-      for (int q = 0; q < kTile; ++q) ty += redy[q];
-      G.s_part[blockIdx.x] = ty;
-    }
+    if (threadIdx.x == 0) G.s_part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
   }
 }
 
@@ -1512,6 +1641,7 @@ struct Launch {
   int B;
   bool uni;     // SpMM over the 4-row union lists
   bool fw;      // F w products of the update kernels on the matrix cores
+  bool wide;    // a slab is 4 GiB or more: 64-bit row offsets in the union SpMM
 };
 
 template <int NI>
@@ -1524,10 +1654,12 @@ void launch_iteration(hipStream_t st, const CgArgs* dA, const Launch& L, Ctx* c)
   if (L.ns == 0) {
     k_cg_spmm<0><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA);
   } else if (L.uni) {
-    k_cg_spmm_u<1><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA);
+    if (L.wide) k_cg_spmm_u<1, true><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA);
+    else k_cg_spmm_u<1, false><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA);
     if (L.ns > 1) {
       SDGP_CHECK_LAUNCH();
-      k_cg_spmm_u<2><<<dim3(L.nbs, L.ns - 1, L.B), kT, 0, st>>>(dA);
+      if (L.wide) k_cg_spmm_u<2, true><<<dim3(L.nbs, L.ns - 1, L.B), kT, 0, st>>>(dA);
+      else k_cg_spmm_u<2, false><<<dim3(L.nbs, L.ns - 1, L.B), kT, 0, st>>>(dA);
     }
   } else {
     k_cg_spmm<1><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA);
@@ -1646,15 +1778,15 @@ struct ShapeGuard {   // leaves trial mode on every exit path
   ~ShapeGuard() { c->in_trial = false; }
 };
 
-// A population's members differ in their entries per row, so its class
-// leaves that out (one tuned shape serves every population of the class).
+// "u16": shapes tuned for the 16-row union lists.  A population's members
+// differ in their entries per row, so its class leaves that out (one tuned shape serves every population of the class).
 std::string tune_key(const Ctx* c, int NI, int ns, int B, int64_t n, int64_t nnz, bool lr, bool pc) {
   const double per_row = std::max(1.0, (double)nnz / (double)std::max<int64_t>(n, 1));
   int lgn = 0;
   while (((int64_t)2 << lgn) <= n) ++lgn;
   const int rb = B > 1 ? -1 : (int)std::lround(2.0 * std::log2(per_row));
   char buf[160];
-  std::snprintf(buf, sizeof(buf), "%s|ni%d|ns%d|b%d|n%d|r%d|lr%d|pc%d", c->arch.c_str(), NI, ns, B > 1 ? 2 : 1,
+  std::snprintf(buf, sizeof(buf), "%s|u16|ni%d|ns%d|b%d|n%d|r%d|lr%d|pc%d", c->arch.c_str(), NI, ns, B > 1 ? 2 : 1,
                 lgn, rb, lr ? 1 : 0, pc ? 1 : 0);
   return buf;
 }
@@ -1677,8 +1809,19 @@ static TuneChoice run_tuner(Ctx* c, const std::vector<CgMember>& mem, const Sort
     return c->trial_ms;
   };
   TuneChoice best;   // the defaults, made explicit
-  best.spmm_blocks = (int)std::min<int64_t>(kMaxNbs, round8(tiles));
   best.union_spmm = (ns > 0 && n >= kUnionMinRows) ? 1 : 0;
+  const int64_t round_u = round8((int64_t)kUnionPerCu * c->cu_count), tiles_u = (n + kUTile - 1) / kUTile;
+  // SpMM grids of a form: resident rounds for the union lists, fixed sizes for the CSR rows
+  auto spmm_grids = [&](int u) {
+    std::vector<int> out;
+    for (int64_t g : u ? std::vector<int64_t>{round_u, 2 * round_u, 4 * round_u, 16 * round_u}
+                       : std::vector<int64_t>{kMaxNbs, 8192, 16384, 65528}) {
+      const int v = (int)std::min<int64_t>({g, (int64_t)65528, round8(u ? tiles_u : tiles)});
+      if (std::find(out.begin(), out.end(), v) == out.end()) out.push_back(v);
+    }
+    return out;
+  };
+  best.spmm_blocks = spmm_grids(best.union_spmm)[0];
   best.fw_mfma = (ns > 0 && n1 > 0) ? 1 : 0;
   const int round1 = update_blocks_per_cu(NI, best.fw_mfma != 0) * c->cu_count;
   best.update_blocks = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)kMaxNbu, (int64_t)round1, round8(tiles)}));
@@ -1699,15 +1842,10 @@ static TuneChoice run_tuner(Ctx* c, const std::vector<CgMember>& mem, const Sort
   // stage 1: SpMM form and grid
   {
     const TuneChoice base = best;
-    std::vector<int> grids;
-    for (int g : {8192, 16384, 32768, 65528}) {
-      const int v = (int)std::min<int64_t>(g, round8(tiles));
-      if (std::find(grids.begin(), grids.end(), v) == grids.end()) grids.push_back(v);
-    }
     std::vector<int> forms = {base.union_spmm};
     if (ns > 0) forms.push_back(1 - base.union_spmm);
     for (int u : forms)
-      for (int g : grids) {
+      for (int g : spmm_grids(u)) {
         if (u == base.union_spmm && g == base.spmm_blocks) continue;
         TuneChoice cand = base;
         cand.union_spmm = u;
@@ -1733,6 +1871,17 @@ static TuneChoice run_tuner(Ctx* c, const std::vector<CgMember>& mem, const Sort
     }
   }
   return best;
+}
+
+// Most entries of any 16-row group (a host copy of the groups' counts).
+static int64_t max_group_nnz(Ctx* c, const Csr& A, const int32_t* sched, int64_t ng) {
+  int64_t* gcnt = c->get<int64_t>(S_CG_UCNT, (size_t)(ng + 1));
+  k_group_nnz<<<(unsigned)((ng + 256) / 256), 256, 0, c->stream>>>(A.n, ng, A.row_ptr, sched, gcnt);
+  SDGP_CHECK_LAUNCH();
+  std::vector<int64_t> h((size_t)(ng + 1));
+  SDGP_HIP(hipMemcpyAsync(h.data(), gcnt, h.size() * sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
+  SDGP_HIP(hipStreamSynchronize(c->stream));
+  return *std::max_element(h.begin(), h.end());
 }
 
 std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, const Sorted& s, const double* ys,
@@ -1808,7 +1957,7 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     }
   }
   const int64_t nbs_cap = sh.spmm_blocks > 0 ? sh.spmm_blocks : kMaxNbs;
-  const int nbs = (int)std::min<int64_t>(nbs_cap, round8(tiles));
+  int nbs = (int)std::min<int64_t>(nbs_cap, round8(tiles));
   // F w products of the update kernels on the matrix cores (measured faster at
   // 16 and at 32 bump functions); 0 per-row broadcasts
   const bool fw = ns > 0 && n1 > 0 && sh.fw_mfma != 0;
@@ -1822,66 +1971,72 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   double* Pp = c->get<double>(S_CG_P, NV * B);
   double* Q = c->get<double>(S_CG_Q, NV * B);
   double* V = (use_pc && keep_v) ? c->get<double>(S_CG_V, NV * B) : nullptr;
-  double* s_part = c->get<double>(S_CG_PART, (size_t)R * nbs * B);
   double* s_red = c->get<double>(S_CG_SRED, (size_t)R * B);
   double* u_part = c->get<double>(S_CG_PART2, (size_t)nu * R * nbu * B);
   double* u_red = c->get<double>(S_CG_G, (size_t)nu * R * B);
   double* w_red = use_pc ? c->get<double>(S_CG_WRED, (size_t)(n1 + 1) * R * B) : nullptr;
   double* p_part = use_lr ? c->get<double>(S_CG_PARTG, (size_t)n1 * R * nbu * B) : nullptr;
   double* p_red = use_lr ? c->get<double>(S_CG_GP, (size_t)n1 * R * B) : nullptr;
-  // 4-row union lists of the shared-gather SpMM (per member): lengths,
-  // exclusive scan on the host (once per solve), columns and values
-  // (automatic from kUnionMinRows rows: below that, building the lists costs
-  // more than the solve saves)
+  // Union lists of the shared-gather SpMM (per member): storage per group by
+  // a scan over the groups' entries, then the lists (automatic from
+  // kUnionMinRows rows: below that, building the lists costs more than the
+  // solve saves)
   bool uni = ns > 0 && (sh.union_spmm > 0 || (sh.union_spmm < 0 && n >= kUnionMinRows));
-  const int64_t ng = (n + 3) / 4;
-  int64_t* urp = nullptr;
-  int32_t* ucol = nullptr;
-  double* uval = nullptr;
+  const int64_t ng = (n + kGR - 1) / kGR;
   std::vector<int64_t> uoff(B + 1, 0);
-  std::vector<int64_t> hp;
-  const unsigned ugb = (unsigned)((ng + 255) / 256);
+  int64_t *gv = nullptr;
+  int32_t *glen = nullptr, *ucol = nullptr;
+  uint32_t *gb = nullptr, *gend = nullptr;
+  double* uval = nullptr;
+  uint16_t* upos = nullptr;
   if (uni) {
-    int32_t* ucnt = c->get<int32_t>(S_CG_UCNT, (size_t)ng * B);
-    for (int m = 0; m < B; ++m) {
-      k_union_count<<<ugb, 256, 0, c->stream>>>(n, ng, mem[m].A.row_ptr, mem[m].A.col, s.sched,
-                                                ucnt + (size_t)m * ng);
-      SDGP_CHECK_LAUNCH();
-    }
-    std::vector<int32_t> hc((size_t)ng * B);
-    SDGP_HIP(hipMemcpyAsync(hc.data(), ucnt, hc.size() * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-    SDGP_HIP(hipStreamSynchronize(c->stream));
-    hp.resize((size_t)(ng + 1) * B);
-    for (int m = 0; m < B; ++m) {
-      int64_t acc = 0;
-      for (int64_t q = 0; q < ng; ++q) {
-        hp[(size_t)m * (ng + 1) + q] = acc;
-        acc += hc[(size_t)m * ng + q];
-      }
-      hp[(size_t)m * (ng + 1) + ng] = acc;
-      require(acc <= mem[m].A.nnz || mem[m].A.nnz < 0, "union lists longer than the matrix");
-      uoff[m + 1] = uoff[m] + acc;
-    }
-    // the lists take 36 B per entry on top of the CSR; in automatic mode the
-    // CSR SpMM is used instead when they would take more than half of the
-    // free device memory (large populations)
+    for (int m = 0; m < B; ++m) require(mem[m].A.nnz >= 0, "the matrix's entry count must be known");
+    // (a group's storage is rounded up as in k_group_nnz)
+    const int64_t pad = 6 * ng + 4;
+    for (int m = 0; m < B; ++m) uoff[m + 1] = (uoff[m] + mem[m].A.nnz + 3 * (mem[m].A.nnz / kBE) + pad + 3) & ~(int64_t)3;
+    const int64_t tot = uoff[B];
+    const int64_t slots = tot / kBE + (ng + 1) * B;
+    // in automatic mode the CSR SpMM is used instead when the lists (14 B per
+    // entry) would take more than half of the free device memory (large
+    // populations) or more than the context's workspace may hold
+    const double need = 14.0 * (double)tot + 4.0 * (double)slots + 24.0 * (double)(ng + 1) * B;
     size_t free_b = 0, total_b = 0;
-    const bool fits = hipMemGetInfo(&free_b, &total_b) != hipSuccess ||
-                      (double)uoff[B] * 36.0 + (double)hp.size() * 8.0 <= 0.5 * (double)free_b;
-    if (!fits && c->union_spmm <= 0) uni = false;   // unless the caller asked for the lists
-  }
-  if (uni) {
-    urp = c->get<int64_t>(S_CG_UPTR, hp.size());
-    SDGP_HIP(hipMemcpyAsync(urp, hp.data(), hp.size() * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
-    ucol = c->get<int32_t>(S_CG_UCOL, (size_t)std::max<int64_t>(uoff[B], 1));
-    uval = c->get<double>(S_CG_UVAL, (size_t)std::max<int64_t>(uoff[B], 1) * 4);
-    for (int m = 0; m < B; ++m) {
-      k_union_fill<<<ugb, 256, 0, c->stream>>>(n, ng, mem[m].A.row_ptr, mem[m].A.col, mem[m].A.val, s.sched,
-                                               urp + (size_t)m * (ng + 1), ucol + uoff[m], uval + 4 * uoff[m]);
-      SDGP_CHECK_LAUNCH();
+    bool fits = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need <= 0.5 * (double)free_b;
+    if (c->arena) fits = fits && 1.25 * need <= (double)(c->arena_cap - c->arena_used);
+    else if (c->cap_bytes > 0) fits = fits && 1.25 * need + (double)c->held_bytes <= (double)c->cap_bytes;
+    if (!fits && c->union_spmm <= 0) uni = false;
+    if (uni && n >= kUnionCheckRows)               // a group's values need 32-bit byte offsets
+      for (int m = 0; m < B && uni; ++m) uni = max_group_nnz(c, mem[m].A, s.sched, ng) < ((int64_t)1 << 29);
+    if (uni) {
+      int64_t* gcnt = c->get<int64_t>(S_CG_UCNT, (size_t)(ng + 1));
+      gv = c->get<int64_t>(S_CG_UPTR, (size_t)(ng + 1) * B);
+      glen = c->get<int32_t>(S_CG_ULEN, (size_t)ng * B);
+      gend = c->get<uint32_t>(S_CG_UEND, (size_t)ng * B);
+      gb = c->get<uint32_t>(S_CG_UBATCH, (size_t)slots);
+      ucol = c->get<int32_t>(S_CG_UCOL, (size_t)tot);
+      uval = c->get<double>(S_CG_UVAL, (size_t)tot);
+      upos = c->get<uint16_t>(S_CG_UPOS, (size_t)tot);
+      size_t tb = 0;
+      SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, gcnt, gv, (int)(ng + 1), c->stream));
+      void* tmp = c->get<char>(S_SORT_TMP, tb);
+      for (int m = 0; m < B; ++m) {
+        int64_t* gvm = gv + (size_t)m * (ng + 1);
+        k_group_nnz<<<(unsigned)((ng + 256) / 256), 256, 0, c->stream>>>(n, ng, mem[m].A.row_ptr, s.sched, gcnt);
+        SDGP_CHECK_LAUNCH();
+        SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, gcnt, gvm, (int)(ng + 1), c->stream));
+        k_group_lists<<<(unsigned)((ng + kGBW - 1) / kGBW), kGBW * kWave, 0, c->stream>>>(
+            n, ng, mem[m].A.row_ptr, mem[m].A.col, mem[m].A.val, s.sched, gvm, glen + (size_t)m * ng,
+            gend + (size_t)m * ng, gb + uoff[m] / kBE + (ng + 1) * m, ucol + uoff[m], uval + uoff[m], upos + uoff[m]);
+        SDGP_CHECK_LAUNCH();
+      }
     }
-    SDGP_HIP(hipStreamSynchronize(c->stream));   // hp is read by the copy above
   }
+  // union-list SpMM: one resident round of blocks unless a grid was chosen
+  // (0.180 / 0.186 ms per launch with one / two rounds at 400,000 points)
+  if (uni)
+    nbs = (int)std::min<int64_t>(sh.spmm_blocks > 0 ? nbs : round8((int64_t)kUnionPerCu * c->cu_count),
+                                 round8((n + kUTile - 1) / kUTile));
+  double* s_part = c->get<double>(S_CG_PART, (size_t)R * nbs * B);
   double* ha = c->get<double>(S_CG_HIST_A, (size_t)max_iter * R * B);
   double* hb = c->get<double>(S_CG_HIST_B, (size_t)max_iter * R * B);
   // per-member state block: doubles rz[2R], rz0[R], bnorm2[R], rr_last[R];
@@ -1926,9 +2081,13 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     A.w_red = w_red ? w_red + (size_t)m * (n1 + 1) * R : nullptr;
     A.p_part = p_part ? p_part + (size_t)m * n1 * R * nbu : nullptr;
     A.p_red = p_red ? p_red + (size_t)m * n1 * R : nullptr;
-    A.urp = uni ? urp + (size_t)m * (ng + 1) : nullptr;
+    A.gv = uni ? gv + (size_t)m * (ng + 1) : nullptr;
+    A.glen = uni ? glen + (size_t)m * ng : nullptr;
+    A.gend = uni ? gend + (size_t)m * ng : nullptr;
+    A.gb = uni ? gb + uoff[m] / kBE + (ng + 1) * m : nullptr;
     A.ucol = uni ? ucol + uoff[m] : nullptr;
-    A.uval = uni ? uval + 4 * uoff[m] : nullptr;
+    A.uval = uni ? uval + uoff[m] : nullptr;
+    A.upos = uni ? upos + uoff[m] : nullptr;
     char* mb = sb + sbytes * m;
     A.st.rz = reinterpret_cast<double*>(mb);
     A.st.rz0 = A.st.rz + 2 * (size_t)R;
@@ -1946,7 +2105,7 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   }
   CgArgs* dA = c->get<CgArgs>(S_CG_ARGS, B);
   SDGP_HIP(hipMemcpyAsync(dA, hA.data(), B * sizeof(CgArgs), hipMemcpyHostToDevice, c->stream));
-  Launch L{nbs, nbu, ns, R, n1, use_pc, use_lr, B, uni, fw};
+  Launch L{nbs, nbu, ns, R, n1, use_pc, use_lr, B, uni, fw, n * kSlab * 8 >= ((int64_t)1 << 32)};
   if (!c->in_trial) {
     c->last_shape.spmm_blocks = nbs;
     c->last_shape.update_blocks = nbu;

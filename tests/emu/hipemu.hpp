@@ -216,12 +216,13 @@ inline int lane() { return g_cur->lane; }
 // DPP row_newbcast:u (control 0x150 + u): every lane of a 16-lane row gets
 // lane u of its row; a source lane that is not live leaves `old`.
 inline int update_dpp(int old, int src, int ctrl, int row_mask, int bank_mask, bool bound_ctrl) {
-  if (ctrl < 0x150 || ctrl > 0x15F || row_mask != 0xF || bank_mask != 0xF || bound_ctrl)
+  const bool ror = ctrl >= 0x121 && ctrl <= 0x12F;   // row_ror:n, lane x gets lane x - n of its row of 16
+  if (((ctrl < 0x150 || ctrl > 0x15F) && !ror) || row_mask != 0xF || bank_mask != 0xF || bound_ctrl)
     fail("update_dpp: control 0x%x (row_mask %x bank_mask %x bound_ctrl %d) is not emulated", ctrl, row_mask,
          bank_mask, (int)bound_ctrl);
   uint64_t m;
   const uint64_t* all = wave_collect(to_bits((uint32_t)src), &m, kDpp);
-  const int s = (lane() & ~15) + (ctrl - 0x150);
+  const int s = (lane() & ~15) + (ror ? (lane() - (ctrl - 0x120)) & 15 : ctrl - 0x150);
   return (m >> s & 1) ? (int)(uint32_t)all[s] : old;
 }
 
@@ -280,6 +281,23 @@ inline d4v mfma_f64_16x16x4(double a, double b, d4v c, int cbsz, int abid, int b
   return d;
 }
 
+// v_mfma_f64_4x4x4_4b: four products D_b[4x4] = A_b[4x4] B_b[4x4] + C_b;
+// lane 16 k + 4 b + x holds A_b[x][k], B_b[k][x] and D_b[k][x].
+inline double mfma_f64_4x4x4(double a, double b, double c, int cbsz, int abid, int blgp) {
+  if (cbsz || abid || blgp) fail("mfma_f64_4x4x4f64 with broadcast controls is not emulated");
+  uint64_t ma, mb;
+  const uint64_t* A = wave_collect(to_bits(a), &ma, kMfmaA);
+  double av[64];
+  for (int i = 0; i < 64; ++i) av[i] = from_bits<double>(A[i]);
+  const uint64_t* Bv = wave_collect(to_bits(b), &mb, kMfmaB);
+  if (ma != ~0ull || mb != ~0ull) fail("matrix-core product with lanes that are not live (mask %llx)",
+                                       (unsigned long long)ma);
+  const int l = lane(), row = l >> 4, blk = (l >> 2) & 3, x = l & 3;
+  double s = c;
+  for (int k = 0; k < 4; ++k) s += av[16 * k + 4 * blk + row] * from_bits<double>(Bv[16 * k + 4 * blk + x]);
+  return s;
+}
+
 }  // namespace emu
 
 #define threadIdx (::emu::g_cur->tid)
@@ -293,6 +311,8 @@ inline d4v mfma_f64_16x16x4(double a, double b, d4v c, int cbsz, int abid, int b
 #define __builtin_amdgcn_mbcnt_lo(m, a) ::emu::mbcnt_lo((m), (a))
 #define __builtin_amdgcn_mbcnt_hi(m, a) ::emu::mbcnt_hi((m), (a))
 #define __builtin_amdgcn_wave_barrier() ::emu::wave_barrier()
+#define __builtin_amdgcn_s_setprio(p) ((void)0)
+#define __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, x, y, z) ::emu::mfma_f64_4x4x4((a), (b), (c), (x), (y), (z))
 #define __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, x, y, z) ::emu::mfma_f64_16x16x4((a), (b), (c), (x), (y), (z))
 
 inline void __syncthreads() { ::emu::block_barrier(); }
