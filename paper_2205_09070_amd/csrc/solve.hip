@@ -8,9 +8,7 @@
 // odd R a one-wavefront-per-row kernel whose 64 lanes hold 64 consecutive
 // columns.  Reductions are deterministic (fixed-order block partials).
 #include <algorithm>
-#include <atomic>
 #include <cmath>
-#include <thread>
 #include <vector>
 
 #include "kernel_math.hpp"
@@ -567,70 +565,193 @@ std::vector<Precond> lowrank_precond_pop(Ctx* c, const Sorted& s, const std::vec
 
 namespace {
 
-// Number of eigenvalues of the symmetric tridiagonal T (d, e) below x
-// (Sturm sequence of the LDL^T pivots of T - xI).
-int sturm_count(const std::vector<double>& d, const std::vector<double>& e, double x) {
-  const int m = (int)d.size();
-  int cnt = 0;
-  double q = d[0] - x;
-  if (q < 0.0) ++cnt;
-  for (int k = 1; k < m; ++k) {
-    if (q == 0.0) q = 1e-300;
-    q = d[k] - x - e[k - 1] * e[k - 1] / q;
-    if (q < 0.0) ++cnt;
-  }
-  return cnt;
-}
-
-// e_1^T ln(T) e_1 for the symmetric positive definite tridiagonal T by the
-// integral ln(theta) = int_0^inf [1/(1+t) - 1/(theta+t)] dt applied to the
-// spectral measure of e_1: with t = exp(s),
-//   e_1^T ln(T) e_1 = int_R t [1/(1+t) - e_1^T (T + tI)^{-1} e_1] ds.
-// The integrand is analytic in the strip |Im s| < pi (poles at
+// Lanczos quadrature of one column per workgroup.  The column's tridiagonal T
+// (d, e) follows from its CG coefficients, d_k = 1/a_k + b_{k-1}/a_{k-1} and
+// e_k = sqrt(b_k)/a_k, and
+//   e_1^T ln(T) e_1 = int_R t [1/(1+t) - e_1^T (T + tI)^{-1} e_1] ds, t = exp(s),
+// which is ln(theta) = int_0^inf [1/(1+t) - 1/(theta+t)] dt on the spectral
+// measure of e_1.  The integrand is analytic in the strip |Im s| < pi (poles at
 // s = ln(theta_j) + i pi), so the trapezoidal rule with step h converges like
 // exp(-2 pi^2 / h); the tails decay like exp(-|s|) beyond the spectrum.
-// e_1^T (T + tI)^{-1} e_1 is the continued fraction of the bottom-up
-// pivots of T + tI (O(m) per node).  Returns NaN if T is not positive
-// definite; lo/hi receive the extreme Ritz values (bisection).
-double quad_log_tridiag(const std::vector<double>& d, const std::vector<double>& e, double* lo, double* hi) {
-  const int m = (int)d.size();
+// e_1^T (T + tI)^{-1} e_1 is the continued fraction of the bottom-up pivots of
+// T + tI.  Nodes are the workgroup's threads (about 210 + 2.5 ln(condition)).
+// The extreme Ritz values, which bound the nodes, come from Sturm counts (signs
+// of the LDL^T pivots of T - xI) at 159 points at once for each of the two,
+// each round cutting the interval by 160.
+// Every chain is serial in k, one division a step (about 0.1 us), so what counts
+// is how many run at once: all nodes of all columns.  On the host (16 threads)
+// the quadrature took 65 ms for the 2000 unit columns of a 2000-point exact
+// evaluation, and 7 ms for 32 probes of 2600 steps.
+constexpr int kSlqT = 320;                      // threads: 5 wavefronts
+constexpr int kSlqH = kSlqT / 2;                // points per extreme Ritz value
+constexpr int kSlqC = 1024;                     // steps staged in LDS at a time
+__global__ __launch_bounds__(kSlqT) void k_slq(const double* __restrict__ ha, const double* __restrict__ hb, int R,
+                                               const int32_t* __restrict__ iters, int cap, double* __restrict__ out) {
+  __shared__ double sd[kSlqC], se2[kSlqC];      // d_k, e_k^2
+  __shared__ double red[kSlqT];
+  __shared__ double iv[4];                      // [lo, hi] of the smallest, of the largest Ritz value
+  __shared__ int hit[2], bad;
+  const int r = 1 + blockIdx.x, t = threadIdx.x;
+  double* o = out + 3 * (int64_t)blockIdx.x;
+  const int m = cap > 0 ? min(iters[r], cap) : iters[r];
+  if (m <= 0) {                                 // uniform
+    if (t == 0) {
+      o[0] = 0.0;
+      o[1] = INFINITY;
+      o[2] = -INFINITY;
+    }
+    return;
+  }
+  auto d_of = [&](int k) {
+    double v = 1.0 / ha[(int64_t)k * R + r];
+    if (k > 0) v += hb[(int64_t)(k - 1) * R + r] / ha[(int64_t)(k - 1) * R + r];
+    return v;
+  };
+  auto e_of = [&](int k) { return k + 1 < m ? sqrt(hb[(int64_t)k * R + r]) / ha[(int64_t)k * R + r] : 0.0; };
+  const int nch = (m + kSlqC - 1) / kSlqC;
+  int held = -1;                                // chunk in LDS (uniform)
+  auto stage = [&](int ch) {
+    if (ch == held) return;
+    __syncthreads();
+    for (int k = ch * kSlqC + t; k < min(m, (ch + 1) * kSlqC); k += kSlqT) {
+      const double e = e_of(k);
+      sd[k - ch * kSlqC] = d_of(k);
+      se2[k - ch * kSlqC] = e * e;
+    }
+    held = ch;
+    __syncthreads();
+  };
   // Gershgorin interval
   double glo = INFINITY, ghi = -INFINITY;
-  for (int k = 0; k < m; ++k) {
-    const double r = (k > 0 ? std::fabs(e[k - 1]) : 0.0) + (k + 1 < m ? std::fabs(e[k]) : 0.0);
-    glo = std::min(glo, d[k] - r);
-    ghi = std::max(ghi, d[k] + r);
+  int nan = 0;
+  for (int k = t; k < m; k += kSlqT) {
+    const double d = d_of(k), rr = (k > 0 ? fabs(e_of(k - 1)) : 0.0) + fabs(e_of(k));
+    if (!isfinite(d) || !isfinite(rr)) nan = 1;
+    glo = fmin(glo, d - rr);
+    ghi = fmax(ghi, d + rr);
   }
-  if (!(ghi > 0.0) || !std::isfinite(glo) || !std::isfinite(ghi)) return NAN;
-  if (sturm_count(d, e, 0.0) != 0) return NAN;          // some theta <= 0
-  // extreme eigenvalues by bisection (relative accuracy 1e-10)
-  double a = std::max(glo, 0.0), b = ghi;
-  for (int it = 0; it < 200 && b - a > 1e-10 * b; ++it) {
-    const double mid = 0.5 * (a + b);
-    if (sturm_count(d, e, mid) >= 1) b = mid; else a = mid;
+  auto block_min = [&](double v) {
+    red[t] = v;
+    __syncthreads();
+    if (t < 64) red[t] = fmin(fmin(fmin(red[t], red[t + 64]), fmin(red[t + 128], red[t + 192])), red[t + 256]);
+    __syncthreads();
+    if (t == 0)
+      for (int k = 1; k < 64; ++k) red[0] = fmin(red[0], red[k]);
+    __syncthreads();
+    const double x = red[0];
+    __syncthreads();
+    return x;
+  };
+  if (t == 0) bad = 0;
+  glo = block_min(glo);
+  ghi = -block_min(-ghi);
+  if (nan) bad = 1;
+  __syncthreads();
+  if (bad || !(ghi > 0.0) || !isfinite(glo) || !isfinite(ghi)) {
+    if (t == 0) {
+      o[0] = NAN;
+      o[1] = o[2] = 0.0;
+    }
+    return;
   }
-  const double tmin = b;
-  a = std::max(glo, 0.0);
-  b = ghi;
-  for (int it = 0; it < 200 && b - a > 1e-10 * b; ++it) {
-    const double mid = 0.5 * (a + b);
-    if (sturm_count(d, e, mid) >= m) b = mid; else a = mid;
+  // pivots of T - xI below zero
+  auto sturm = [&](double x) {
+    int cnt = 0;
+    double q = 1.0, ep = 0.0;                   // first step: d_0 - x
+    for (int ch = 0; ch < nch; ++ch) {
+      stage(ch);
+      const int e = min(m - ch * kSlqC, kSlqC);
+      for (int k = 0; k < e; ++k) {
+        if (q == 0.0) q = 1e-300;
+        q = sd[k] - x - ep / q;
+        ep = se2[k];
+        if (q < 0.0) ++cnt;
+      }
+    }
+    return cnt;
+  };
+  if (t == 0) {
+    iv[0] = iv[2] = fmax(glo, 0.0);
+    iv[1] = iv[3] = ghi;
   }
-  const double tmax = b;
-  *lo = tmin;
-  *hi = tmax;
-  if (!(tmin > 0.0)) return NAN;
+  __syncthreads();
+  // first round: thread 0 of the lower half counts at 0 (some theta <= 0: no
+  // logarithm); then point i of a half at the (i + 1)/160 part of its interval
+  for (int round = 0; round < 64; ++round) {
+    const double a0 = iv[0], b0 = iv[1], a1 = iv[2], b1 = iv[3];
+    const bool go = b0 - a0 > 1e-10 * b0 || b1 - a1 > 1e-10 * b1;
+    if (!go && round > 0) break;
+    const int half = t >= kSlqH ? 1 : 0, i = t - half * kSlqH;
+    const double a = half ? a1 : a0, b = half ? b1 : b0;
+    const bool zero = i == kSlqH - 1;           // the last point of a half is the interval's end: 0 instead
+    const double x = zero ? 0.0 : a + (b - a) * ((i + 1) / (double)kSlqH);
+    __syncthreads();                            // iv is read
+    if (t < 2) hit[t] = kSlqH;
+    const int cnt = sturm(x);
+    __syncthreads();
+    if (zero) {
+      if (cnt != 0) bad = 1;
+    } else if (cnt >= (half ? m : 1)) {
+      atomicMin(&hit[half], i);
+    }
+    __syncthreads();
+    if (bad) {
+      if (t == 0) {
+        o[0] = NAN;
+        o[1] = o[2] = 0.0;
+      }
+      return;
+    }
+    if (t < 2) {
+      const double la = t ? a1 : a0, lb = t ? b1 : b0;
+      const int h = hit[t];                     // first point at or above the Ritz value
+      if (h < kSlqH - 1) iv[2 * t + 1] = la + (lb - la) * ((h + 1) / (double)kSlqH);
+      const int below = h < kSlqH ? h : kSlqH - 1;
+      if (below > 0) iv[2 * t] = la + (lb - la) * (below / (double)kSlqH);
+    }
+    __syncthreads();
+  }
+  const double tmin = iv[1], tmax = iv[3];
+  if (!(tmin > 0.0)) {
+    if (t == 0) {
+      o[0] = NAN;
+      o[1] = tmin;
+      o[2] = tmax;
+    }
+    return;
+  }
   const double h = 0.4;
-  const double s0 = std::log(tmin) - 42.0, s1 = std::log(tmax) + 42.0;
-  const int nodes = (int)std::ceil((s1 - s0) / h);
+  const double s0 = log(tmin) - 42.0, s1 = log(tmax) + 42.0;
+  const int nodes = (int)ceil((s1 - s0) / h);
   double acc = 0.0;
-  for (int j = 0; j <= nodes; ++j) {
-    const double t = std::exp(s0 + j * h);
-    double f = d[m - 1] + t;
-    for (int k = m - 2; k >= 0; --k) f = d[k] + t - e[k] * e[k] / f;
-    acc += t * (1.0 / (1.0 + t) - 1.0 / f);
+  for (int j0 = 0; j0 <= nodes; j0 += kSlqT) {
+    const int j = j0 + t;
+    const double x = exp(s0 + min(j, nodes) * h);
+    double f = 1.0;
+    for (int ch = nch - 1; ch >= 0; --ch) {
+      stage(ch);
+      int k = min(m - ch * kSlqC, kSlqC) - 1;
+      if (ch == nch - 1) {
+        f = sd[k] + x;
+        --k;
+      }
+      for (; k >= 0; --k) f = sd[k] + x - se2[k] / f;
+    }
+    if (j <= nodes) acc += x * (1.0 / (1.0 + x) - 1.0 / f);
   }
-  return h * acc;
+  __syncthreads();
+  red[t] = acc;
+  __syncthreads();
+  if (t < 64) red[t] = ((red[t] + red[t + 64]) + (red[t + 128] + red[t + 192])) + red[t + 256];
+  __syncthreads();
+  if (t < 64) {
+    const double s = wave_sum(red[t]);
+    if (t == 0) {
+      o[0] = h * s;
+      o[1] = tmin;
+      o[2] = tmax;
+    }
+  }
 }
 
 }  // namespace
@@ -644,64 +765,24 @@ void slq_from_cg(Ctx* c, const CgResult& cg, int kind, int P, int64_t n, int lan
     *logdet = 0.0; *stderr_out = 0.0; *ritz_min = 0.0; *ritz_max = 0.0;
     return;
   }
-  std::vector<int32_t> its(cg.R);
-  std::vector<double> w0(cg.R);
-  SDGP_HIP(hipMemcpyAsync(its.data(), cg.col_iters, cg.R * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+  double* dq = c->get<double>(S_SLQ_OUT, (size_t)ncols * 3);
+  k_slq<<<(unsigned)ncols, kSlqT, 0, c->stream>>>(cg.hist_a, cg.hist_b, cg.R, cg.col_iters, lanczos_steps, dq);
+  SDGP_CHECK_LAUNCH();
+  std::vector<double> w0(cg.R), qlh((size_t)ncols * 3);   // (quadrature, smallest, largest Ritz value) per column
   SDGP_HIP(hipMemcpyAsync(w0.data(), cg.rz0, cg.R * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  SDGP_HIP(hipMemcpyAsync(qlh.data(), dq, qlh.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   SDGP_HIP(hipStreamSynchronize(c->stream));
-  int mmax = 0;
-  for (int r = 1; r < cg.R; ++r) mmax = std::max(mmax, its[r]);
-  if (lanczos_steps > 0) mmax = std::min(mmax, lanczos_steps);
-  // coefficient history rows 0..mmax-1 (all columns) to the host
-  std::vector<double> ha((size_t)std::max(mmax, 1) * cg.R), hb((size_t)std::max(mmax, 1) * cg.R);
-  if (mmax > 0) {
-    SDGP_HIP(hipMemcpyAsync(ha.data(), cg.hist_a, (size_t)mmax * cg.R * sizeof(double), hipMemcpyDeviceToHost,
-                            c->stream));
-    SDGP_HIP(hipMemcpyAsync(hb.data(), cg.hist_b, (size_t)mmax * cg.R * sizeof(double), hipMemcpyDeviceToHost,
-                            c->stream));
-    SDGP_HIP(hipStreamSynchronize(c->stream));
-  }
-  std::vector<double> q(ncols), lo(ncols), hi(ncols);
-  auto work = [&](int p) {
-    const int r = 1 + p;
-    int m = its[r];
-    if (lanczos_steps > 0) m = std::min(m, lanczos_steps);
-    if (m <= 0) { q[p] = 0.0; lo[p] = INFINITY; hi[p] = -INFINITY; return; }
-    std::vector<double> d(m), e(std::max(m - 1, 1), 0.0);
-    for (int k = 0; k < m; ++k) {
-      const double ak = ha[(size_t)k * cg.R + r];
-      double dk = 1.0 / ak;
-      if (k > 0) dk += hb[(size_t)(k - 1) * cg.R + r] / ha[(size_t)(k - 1) * cg.R + r];
-      d[k] = dk;
-      if (k + 1 < m) e[k] = std::sqrt(hb[(size_t)k * cg.R + r]) / ak;
-    }
-    q[p] = quad_log_tridiag(d, e, &lo[p], &hi[p]);
-  };
-  unsigned hw = std::thread::hardware_concurrency();
-  int nt = (int)std::max(1u, std::min(hw == 0 ? 1u : hw, 16u));
-  nt = std::min(nt, ncols);
-  if (nt <= 1) {
-    for (int p = 0; p < ncols; ++p) work(p);
-  } else {
-    std::vector<std::thread> th;
-    std::atomic<int> next(0);
-    for (int t = 0; t < nt; ++t)
-      th.emplace_back([&] {
-        for (int p = next.fetch_add(1); p < ncols; p = next.fetch_add(1)) work(p);
-      });
-    for (auto& t : th) t.join();
-  }
   // weight of probe p: |M^{-1/2} b_p|^2 = b_p^T M^{-1} b_p (|z|^2 without a
   // preconditioner: n for Rademacher, 1 for unit vectors)
   double sum = 0.0, sum2 = 0.0, mn = INFINITY, mx = -INFINITY;
   bool bad = false;
   for (int p = 0; p < ncols; ++p) {
-    const double v = w0[1 + p] * q[p];
+    const double v = w0[1 + p] * qlh[3 * p];
     if (!std::isfinite(v)) bad = true;
     sum += v;
     sum2 += v * v;
-    mn = std::min(mn, lo[p]);
-    mx = std::max(mx, hi[p]);
+    mn = std::min(mn, qlh[3 * p + 1]);
+    mx = std::max(mx, qlh[3 * p + 2]);
   }
   if (bad) throw Error(SDGP_ERR_NOT_SPD, "Lanczos quadrature met a non-positive Ritz value");
   if (kind == PK_IDENTITY) {

@@ -388,6 +388,12 @@ inline double atomicAdd(double* p, double v) {
   }
 }
 template <class T>
+inline T atomicMin(T* p, T v) {
+  const T old = *p;
+  if (v < old) *p = v;
+  return old;
+}
+template <class T>
 inline T atomicOr(T* p, T v) {
   return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST);
 }
