@@ -194,6 +194,11 @@ sdgp_status sdgp_set_timing(sdgp_ctx* ctx, int enable);
  * the context may hold; a call that would grow it further fails with
  * SDGP_ERR_OOM before allocating (its outputs are then unspecified, the
  * context stays usable).
+ * Small point sets (up to 10048 points, by a rule on points, entries and
+ * columns) are solved without the block CG: one workgroup per few columns
+ * runs their whole solve in one launch.  The launch-shape options and "graph"
+ * do not apply there; setting any launch-shape option, or "autotune" 2, takes
+ * the block CG at every size.
  * "timing" and "graph" leave the results bitwise unchanged;
  * "union_spmm", "fw_mfma", "update_blocks" and "spmm_blocks" change only the
  * order of floating-point sums
@@ -202,7 +207,8 @@ sdgp_status sdgp_set_timing(sdgp_ctx* ctx, int enable);
 sdgp_status sdgp_set_option(sdgp_ctx* ctx, const char* name, int64_t value);
 
 /* Reads a context option (the names of sdgp_set_option) or the launch
- * shape of the context's last CG solve: "last_spmm_blocks",
+ * shape of the context's last CG solve (small point sets: "last_spmm_blocks"
+ * workgroups, the others 0): "last_spmm_blocks",
  * "last_update_blocks", "last_union_spmm" (0/1), "last_fw_mfma" (0/1) and
  * "last_tuned" (0: options or defaults, 1: tuned shape read from the store,
  * 2: tuned during that call); "last_y_tail": iterations the last solve ran

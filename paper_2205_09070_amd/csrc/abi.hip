@@ -595,15 +595,8 @@ sdgp_status sdgp_posterior_mean_var(sdgp_ctx* ctx, const sdgp_kernel_desc* desc,
     Precond pc;
     const bool use_pc = est->precond == SDGP_PRECOND_LOWRANK && desc->combine == SDGP_COMBINE_SUM;
     if (use_pc) pc = lowrank_precond(ctx, s, as.kp, as.b);
-    CgResult cg = block_cg(ctx, as.A, s, ys, PK_NONE, 0, 0, est->cg_rtol, est->cg_max_iter, nullptr, 0,
-                           use_pc ? &pc : nullptr, false, nullptr);
-    if (cg.not_spd) throw Error(SDGP_ERR_NOT_SPD, "CG met p^T A p <= 0: the covariance is not positive definite");
-    conv = cg.converged;
-    spmm(ctx, K0, cg.X, 1, mean_out);
-    bool c2 = true;
-    posterior_variance(ctx, as.A, s, K0, kxx, est->cg_rtol, est->cg_max_iter, use_pc ? &pc : nullptr, var_out,
-                       &c2);
-    conv = conv && c2;
+    posterior_solve(ctx, as.A, s, ys, K0, kxx, est->cg_rtol, est->cg_max_iter, use_pc ? &pc : nullptr, mean_out,
+                    var_out, &conv);
     SDGP_HIP(hipStreamSynchronize(ctx->stream));
   });
   if (st != SDGP_OK) return st;

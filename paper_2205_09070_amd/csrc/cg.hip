@@ -1925,12 +1925,20 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   const size_t NV = (size_t)ny + (size_t)ns * n * kSlab;   // doubles per vector block
   require(NV >= (size_t)n * R, "layout");
   const int64_t tiles = (n + kTile - 1) / kTile;
+  const bool user_shape = c->spmm_blocks > 0 || c->update_blocks > 0 || c->union_spmm >= 0 || c->fw_mfma >= 0;
+  // Small point sets: one workgroup per few columns (colcg.hip), unless the
+  // caller asks for a launch shape of the block CG or for tuning it
+  if (column_cg_chosen(c)) {
+    int64_t nnz = 0;
+    for (const auto& mm : mem) nnz = std::max<int64_t>(nnz, mm.A.nnz);
+    if (column_cg_applies(c, n, nnz, R, B, n1, use_pc && keep_v, max_iter))
+      return column_cg(c, mem, s, ys, kind, R, seed, rtol, prt, max_iter, dense_rhs, keep_v);
+  }
   // Launch shape: a tuner trial's candidate; else the context options when
   // any is set; else the tuned shape of this problem class (tuned now when
   // the store has none); else the defaults.
   TuneChoice sh;
   int tuned = 0;
-  const bool user_shape = c->spmm_blocks > 0 || c->update_blocks > 0 || c->union_spmm >= 0 || c->fw_mfma >= 0;
   if (c->in_trial) {
     sh = c->trial;
   } else if (user_shape) {

@@ -100,6 +100,8 @@ enum Slot {
   S_POP_ARGS, S_POP_RARGS, S_POP_BP, S_POP_F, S_POP_M, S_POP_CM, S_POP_RUNCNT, S_POP_RUNPOS, S_POP_RUNPTR, S_POP_RUNS,
   S_POP_IVCNT, S_POP_IVPTR, S_POP_IV, S_POP_ROWNNZ, S_POP_SCAN, S_POP_ROWPTR, S_POP_COL, S_POP_VAL, S_POP_CAND,
   S_POP_GRAM, S_POP_SINV,
+  // column CG (small point sets)
+  S_COL_IDX, S_COL_OFF, S_COL_VAL, S_COL_COL, S_COL_FT, S_COL_STATE,
   S_NUM
 };
 
@@ -331,6 +333,18 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
                                      const double* ys, int kind, int P, uint64_t seed, double rtol,
                                      int max_iter, const double* dense_rhs, int dense_R, bool keep_v,
                                      bool use_graph, double probe_rtol = 0.0);
+// Column CG (colcg.hip): the same solves, one workgroup per few columns, for
+// point sets whose search directions fit in LDS.  R: columns of the kind.
+// The context leaves the solver's form open (no launch shape of the block CG
+// asked for, none being tuned).
+inline bool column_cg_chosen(const Ctx* c) {
+  return !c->in_trial && c->autotune != 2 && c->spmm_blocks <= 0 && c->update_blocks <= 0 && c->union_spmm < 0 &&
+         c->fw_mfma < 0;
+}
+bool column_cg_applies(const Ctx* c, int64_t n, int64_t nnz, int R, int B, int n1, bool keep_v, int max_iter);
+std::vector<CgResult> column_cg(Ctx* c, const std::vector<CgMember>& mem, const Sorted& s, const double* ys, int kind,
+                                int R, uint64_t seed, double rtol, double prtol, int max_iter,
+                                const double* dense_rhs, bool keep_v);
 Precond lowrank_precond(Ctx* c, const Sorted& s, const KParams& kp, const Bumps& b);
 // The same for every member of a population (one Gram launch, grid z =
 // member); the members' bump values are contiguous from F0 with stride
@@ -355,10 +369,11 @@ void slq_from_cg(Ctx* c, const CgResult& cg, int kind, int P, int64_t n,
 double dot_device(Ctx* c, const double* a, int64_t stride_a, const double* b,
                   int64_t stride_b, int64_t n);
 void probe_bits(Ctx* c, const Sorted& s, int P, uint64_t seed, uint64_t* zbits);
-// var[t] = kxx[t] - kappa_t^T A^{-1} kappa_t, by block CG over chunks of 64
-// test columns.
-void posterior_variance(Ctx* c, const Csr& A, const Sorted& s, const Csr& K0, const double* kxx, double rtol,
-                        int max_iter, const Precond* pc, double* var, bool* converged);
+// mean[t] = kappa_t^T A^{-1} y and var[t] = kxx[t] - kappa_t^T A^{-1} kappa_t:
+// y by itself and the test columns in chunks of 64 (block CG), or y together
+// with up to 1023 test columns at a time (column CG).
+void posterior_solve(Ctx* c, const Csr& A, const Sorted& s, const double* ys, const Csr& K0, const double* kxx,
+                     double rtol, int max_iter, const Precond* pc, double* mean, double* var, bool* converged);
 
 // ---------------------------------------------------------------------------
 // Adjoint (adjoint.hip)

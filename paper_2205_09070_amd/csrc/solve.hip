@@ -214,27 +214,45 @@ __global__ void k_probe_bits(const int32_t* __restrict__ perm, int64_t n, int P,
   bits[s] = m;
 }
 
-// Dense right-hand sides B[b][j] = kappa[t0 + j, b] for a chunk of test rows
-// (B zeroed beforehand; every (b, j) is written at most once).
+// Column 0 of the row-major block B [n][ld].
+__global__ void k_put_column(const double* __restrict__ v, int64_t n, int ld, double* __restrict__ B) {
+  const int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (a < n) B[a * ld] = v[a];
+}
+
+// mean[t] = sum_b kappa[t, b] X[b][0], one wavefront per test row.
+__global__ void k_mean_rows(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                            const double* __restrict__ val, int64_t nq, int ld, const double* __restrict__ X,
+                            double* __restrict__ mean) {
+  const int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+  if (t >= nq) return;
+  double s = 0.0;
+  for (int64_t k = rp[t] + lane_id(); k < rp[t + 1]; k += kWave) s += val[k] * X[(int64_t)col[k] * ld];
+  s = wave_sum(s);
+  if (lane_id() == 0) mean[t] = s;
+}
+
+// Dense right-hand sides B[b][j] = kappa[t0 + j, b] for a chunk of Rc test rows
+// (B, row stride ld, zeroed beforehand; every (b, j) is written at most once).
 __global__ void k_scatter_chunk(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                const double* __restrict__ val, int64_t t0, int Rc, int64_t nq,
+                                const double* __restrict__ val, int64_t t0, int Rc, int64_t nq, int ld,
                                 double* __restrict__ B) {
   const int64_t j = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   if (j >= Rc || t0 + j >= nq) return;
   const int64_t t = t0 + j;
-  for (int64_t k = rp[t] + lane_id(); k < rp[t + 1]; k += kWave) B[(int64_t)col[k] * Rc + j] = val[k];
+  for (int64_t k = rp[t] + lane_id(); k < rp[t + 1]; k += kWave) B[(int64_t)col[k] * ld + j] = val[k];
 }
 
 // var[t] = kxx[t] - sum_b kappa[t, b] V[b][j] for the chunk's test rows.
 __global__ void k_rowdot_chunk(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                               const double* __restrict__ val, int64_t t0, int Rc, int64_t nq,
+                               const double* __restrict__ val, int64_t t0, int Rc, int64_t nq, int ld,
                                const double* __restrict__ V, const double* __restrict__ kxx,
                                double* __restrict__ var) {
   const int64_t j = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   if (j >= Rc || t0 + j >= nq) return;
   const int64_t t = t0 + j;
   double s = 0.0;
-  for (int64_t k = rp[t] + lane_id(); k < rp[t + 1]; k += kWave) s += val[k] * V[(int64_t)col[k] * Rc + j];
+  for (int64_t k = rp[t] + lane_id(); k < rp[t + 1]; k += kWave) s += val[k] * V[(int64_t)col[k] * ld + j];
   s = wave_sum(s);
   if (lane_id() == 0) var[t] = kxx[t] - s;
 }
@@ -292,21 +310,44 @@ __global__ void k_taylor_step(int64_t len, const double* __restrict__ Z, const d
 
 }  // namespace
 
-void posterior_variance(Ctx* c, const Csr& A, const Sorted& s, const Csr& K0, const double* kxx, double rtol,
-                        int max_iter, const Precond* pc, double* var, bool* converged) {
+void posterior_solve(Ctx* c, const Csr& A, const Sorted& s, const double* ys, const Csr& K0, const double* kxx,
+                     double rtol, int max_iter, const Precond* pc, double* mean, double* var, bool* converged) {
   const int64_t n = A.n, n0 = K0.n;
+  const char* bad = "CG met p^T A p <= 0: the covariance is not positive definite";
   *converged = true;
-  for (int64_t t0 = 0; t0 < n0; t0 += kWave) {
-    const int Rc = (int)std::min<int64_t>(kWave, n0 - t0);
+  // Column CG: y is column 0 of the first chunk, and a chunk fills the GPU's
+  // CUs with columns (chunks of 64 leave most of them idle)
+  const int wide = (int)std::min<int64_t>(1023, n0);
+  const int n1 = pc ? pc->n1 : 0;
+  const bool cols = column_cg_chosen(c) && column_cg_applies(c, n, A.nnz, 1 + wide, 1, n1, true, max_iter);
+  const int step = cols ? wide : kWave;
+  if (!cols) {
+    CgResult cg = block_cg(c, A, s, ys, PK_NONE, 0, 0, rtol, max_iter, nullptr, 0, pc, false, nullptr);
+    if (cg.not_spd) throw Error(SDGP_ERR_NOT_SPD, bad);
+    *converged = cg.converged;
+    spmm(c, K0, cg.X, 1, mean);
+  }
+  for (int64_t t0 = 0; t0 < n0; t0 += step) {
+    const int Rt = (int)std::min<int64_t>(step, n0 - t0);
+    const int y0 = cols && t0 == 0 ? 1 : 0;        // columns before the test columns
+    const int Rc = Rt + y0;
     double* B = c->get<double>(S_POST, (size_t)n * Rc);
     SDGP_HIP(hipMemsetAsync(B, 0, (size_t)n * Rc * sizeof(double), c->stream));
-    const unsigned g = (unsigned)((Rc + 3) / 4);
-    k_scatter_chunk<<<g, 256, 0, c->stream>>>(K0.row_ptr, K0.col, K0.val, t0, Rc, n0, B);
+    if (y0) {
+      k_put_column<<<(unsigned)((n + 255) / 256), 256, 0, c->stream>>>(ys, n, Rc, B);
+      SDGP_CHECK_LAUNCH();
+    }
+    const unsigned g = (unsigned)((Rt + 3) / 4);
+    k_scatter_chunk<<<g, 256, 0, c->stream>>>(K0.row_ptr, K0.col, K0.val, t0, Rt, n0, Rc, B + y0);
     SDGP_CHECK_LAUNCH();
     CgResult cg = block_cg(c, A, s, nullptr, PK_DENSE, 0, 0, rtol, max_iter, B, Rc, pc, false, nullptr);
-    if (cg.not_spd) throw Error(SDGP_ERR_NOT_SPD, "CG met p^T A p <= 0: the covariance is not positive definite");
+    if (cg.not_spd) throw Error(SDGP_ERR_NOT_SPD, bad);
     if (!cg.converged) *converged = false;
-    k_rowdot_chunk<<<g, 256, 0, c->stream>>>(K0.row_ptr, K0.col, K0.val, t0, Rc, n0, cg.X, kxx, var);
+    if (y0) {
+      k_mean_rows<<<(unsigned)((n0 + 3) / 4), 256, 0, c->stream>>>(K0.row_ptr, K0.col, K0.val, n0, Rc, cg.X, mean);
+      SDGP_CHECK_LAUNCH();
+    }
+    k_rowdot_chunk<<<g, 256, 0, c->stream>>>(K0.row_ptr, K0.col, K0.val, t0, Rt, n0, Rc, cg.X + y0, kxx, var);
     SDGP_CHECK_LAUNCH();
   }
 }

@@ -312,6 +312,8 @@ inline double mfma_f64_4x4x4(double a, double b, double c, int cbsz, int abid, i
 #define __builtin_amdgcn_mbcnt_hi(m, a) ::emu::mbcnt_hi((m), (a))
 #define __builtin_amdgcn_wave_barrier() ::emu::wave_barrier()
 #define __builtin_amdgcn_s_setprio(p) ((void)0)
+#define __builtin_amdgcn_s_barrier() ::emu::block_barrier()
+#define __builtin_amdgcn_fence(...) ((void)0)
 #define __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, x, y, z) ::emu::mfma_f64_4x4x4((a), (b), (c), (x), (y), (z))
 #define __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, x, y, z) ::emu::mfma_f64_16x16x4((a), (b), (c), (x), (y), (z))
 
