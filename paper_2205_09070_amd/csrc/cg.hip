@@ -75,6 +75,7 @@ struct CgArgs {
   double *X, *Rr, *P, *Q, *V; // slab layout (V: M^{-1} b, may be null)
   const int32_t* sched;       // SpMM row order (may be null)
   const double* F;            // [n][n1] sorted bump values
+  const uint8_t* fz;          // [(n + 15) / 16] whether a tile of 16 rows holds a bump value other than 0
   const double* Sinv;         // [n1][n1] (c I + F^T F)^{-1}
   int n1;
   int use_pc;                 // z = M^{-1} r, M = c I + F F^T
@@ -897,6 +898,22 @@ __device__ void put_yfold_partials(const CgArgs& A, double* red, bool has0, doub
     }
 }
 
+// Tiles of 16 rows without bump values.  A bump function covers a small part of
+// the points (about 2% at 64 balls of radius 0.03 - 0.06 in the unit cube), so
+// most tiles of F are zero (sweep_tiles).  Bound by one read of F, once a
+// solve; one wavefront per tile.
+__global__ __launch_bounds__(kT) void k_cg_ftiles(const CgArgs* __restrict__ AA, uint8_t* __restrict__ fz, int64_t ld) {
+  const CgArgs& A = AA[blockIdx.z];
+  const int64_t t = (int64_t)blockIdx.x * (kT / kWave) + (threadIdx.x >> 6);
+  if (t * 16 >= A.n) return;
+  const GL double* F = (const GL double*)A.F;
+  const int64_t e1 = min(A.n, (t + 1) * 16) * A.n1;
+  bool any = false;
+  for (int64_t e = t * 16 * A.n1 + lane_id(); e < e1; e += kWave) any |= !(F[e] == 0.0);
+  const bool hit = ballot64(any) != 0;
+  if (lane_id() == 0) fz[(int64_t)blockIdx.z * ld + t] = hit ? 1 : 0;
+}
+
 __device__ __forceinline__ double pick4(const d4& v, int q) {
   return q == 0 ? v[0] : (q == 1 ? v[1] : (q == 2 ? v[2] : v[3]));
 }
@@ -911,6 +928,38 @@ __device__ __forceinline__ int64_t tile_steps(const CgArgs& A) {
 __device__ __forceinline__ int64_t wave_base(const CgArgs& A, int64_t k) {
   return (blockIdx.x + k * (int64_t)A.nbu) * kBlockRows + (threadIdx.x >> 6) * kWaveRows;
 }
+
+// The wavefront's tiles, step by step.  FW 1: all of them.  FW 2: in one pass
+// those without bump values, in another those with (has).  A tile without needs
+// neither F's loads nor its products: F is 14 to 24% of these passes' bytes, and
+// few tiles hold any of it.  Two passes rather than a branch in one: a branch
+// keeps the accumulators of F^T v live beside the plain tiles' loads, and n1 = 32
+// then spills 70 registers (a 4-D iteration took 1.40 ms).  Iteration with FW 1
+// -> FW 2: 1.19 -> 1.06 ms (10^6 points in 4-D, 32 bumps), 0.411 -> 0.407 ms
+// (4 10^5 points in 3-D, 16).  With one tile per wavefront the flag's load only
+// delays the tile's own (2 10^4 points: 60 -> 63 us), so FW 2 is taken from two
+// tiles on.
+template <int FW>
+struct Sweep {
+  int64_t k = 0;        // FW 1: the next step; FW 2: the step after the 64 of m
+  uint64_t m = 0;       // FW 2: steps k - 64 + bit to do
+  __device__ __forceinline__ bool next(const CgArgs& A, int64_t nst, bool has, int64_t& base) {
+    if (FW == 1) {
+      if (k >= nst) return false;
+      base = wave_base(A, k++);
+      return base < A.n;                            // uniform over the wavefront
+    }
+    for (; m == 0; k += kWave) {
+      if (k >= nst) return false;
+      const int64_t mine = wave_base(A, k + lane_id());
+      const bool in = k + lane_id() < nst && mine < A.n;
+      m = ballot64(in && (((const GL uint8_t*)A.fz)[mine >> 4] != 0) == has);
+    }
+    base = wave_base(A, k - kWave + __builtin_ctzll(m));
+    m &= m - 1;
+    return true;
+  }
+};
 
 // Per-column scalars are computed once per block into LDS by the column's
 // owner thread (slab blocks: thread cl < 32 for column 1 + 32 s + cl;
@@ -1008,7 +1057,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NI <= 32 ? 3
   const bool lr = NI > 0 && A.lowrank_op;
   const bool pc = NI > 0 && A.use_pc;
   // matrix-core launches have no column-0 blocks: slab 0 also owns column 0
-  const bool yfold = FW == 1 && !ycol && blockIdx.y == 0;
+  const bool yfold = FW > 0 && !ycol && blockIdx.y == 0;
   if ((int)threadIdx.x < (ycol ? 1 : (yfold ? kSC : kSlab))) {
     const int cl = threadIdx.x;
     const int rc = col_of(A, ycol, cl);
@@ -1084,71 +1133,75 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NI <= 32 ? 3
   d4 acc[NT > 0 ? NT : 1][2];
 #pragma unroll
   for (int mt = 0; mt < (NT > 0 ? NT : 1); ++mt) acc[mt][0] = acc[mt][1] = d4{0.0, 0.0, 0.0, 0.0};
-  if (FW == 1 && __any(mine)) {
+  if (FW > 0 && __any(mine)) {
     // F (F^T p) per 16-row wavefront tile on the matrix cores
     constexpr int NS = (NI + 3) / 4;
     const int g = lane_id() >> 4;
     const int64_t nst = tile_steps(A);
-    for (int64_t k = 0; k < nst; ++k) {
-      const int64_t base = wave_base(A, k);
-      if (base >= A.n) break;                       // uniform over the wavefront
-      d4 ce = {0.0, 0.0, 0.0, 0.0}, cd = {0.0, 0.0, 0.0, 0.0}, cy = {0.0, 0.0, 0.0, 0.0};
-      if (NS > 0 && lr) fw_tile_y<NS>(G.F, A.n1, A.n, base, s_gp, yfold, ce, cd, cy);
-      // row-steps in pairs: both steps' loads before either step's stores,
-      // then the arithmetic in row-step order (as in the p-update pass)
 #pragma unroll
-      for (int h = 0; h < 4 / kGS; ++h) {
-        int64_t ar[kGS];
-        bool in[kGS], iny[kGS];
-        dv2 qv[kGS], rv[kGS];
-        double qyv[kGS], ryv[kGS];
-        double f[kGS][NT > 0 ? NT : 1];
+    for (int pass = FW == 2 ? 0 : 1; pass < 2; ++pass) {
+      const bool kNz = pass == 1;                   // the tiles hold bump values
+      Sweep<FW> sw;
+      int64_t base;
+      while (sw.next(A, nst, kNz, base)) {
+        d4 ce = {0.0, 0.0, 0.0, 0.0}, cd = {0.0, 0.0, 0.0, 0.0}, cy = {0.0, 0.0, 0.0, 0.0};
+        if (NS > 0 && lr && kNz) fw_tile_y<NS>(G.F, A.n1, A.n, base, s_gp, yfold, ce, cd, cy);
+        // row-steps in pairs: both steps' loads before either step's stores,
+        // then the arithmetic in row-step order (as in the p-update pass)
 #pragma unroll
-        for (int e = 0; e < kGS; ++e) {
-          const int64_t a = base + 4 * (kGS * h + e) + g;
-          ar[e] = a;
-          in[e] = a < A.n;
-          iny[e] = acty && jl == 0 && in[e];        // column 0 of row a
-          qyv[e] = iny[e] ? G.Q[a] : 0.0;
-          ryv[e] = iny[e] ? G.Rr[a] : 0.0;
-          qv[e] = rv[e] = dv2{0.0, 0.0};
-          if (in[e]) {
-            const int64_t o = elem(A, false, a);
-            qv[e] = ld_s(G.Q + o);
-            rv[e] = ld_s(G.Rr + o);
+        for (int h = 0; h < 4 / kGS; ++h) {
+          int64_t ar[kGS];
+          bool in[kGS], iny[kGS];
+          dv2 qv[kGS], rv[kGS];
+          double qyv[kGS], ryv[kGS];
+          double f[kGS][NT > 0 ? NT : 1];
+#pragma unroll
+          for (int e = 0; e < kGS; ++e) {
+            const int64_t a = base + 4 * (kGS * h + e) + g;
+            ar[e] = a;
+            in[e] = a < A.n;
+            iny[e] = acty && jl == 0 && in[e];        // column 0 of row a
+            qyv[e] = iny[e] ? G.Q[a] : 0.0;
+            ryv[e] = iny[e] ? G.Rr[a] : 0.0;
+            qv[e] = rv[e] = dv2{0.0, 0.0};
+            if (in[e]) {
+              const int64_t o = elem(A, false, a);
+              qv[e] = ld_s(G.Q + o);
+              rv[e] = ld_s(G.Rr + o);
+            }
+            if (NT > 0 && pc && kNz) load_f<NT>(A, in[e] ? a : -1, f[e]);
           }
-          if (NT > 0 && pc) load_f<NT>(A, in[e] ? a : -1, f[e]);
-        }
 #pragma unroll
-        for (int e = 0; e < kGS; ++e) {
-          const int st = kGS * h + e;
-          const int64_t a = ar[e];
-          double ry = 0.0;
-          if (iny[e]) {
-            const double qy = qyv[e] + pick4(cy, st);
-            ry = ryv[e] - aly * qy;
-            G.Rr[a] = ry;
-            rry += ry * ry;
-          }
-          dv2 r = {0.0, 0.0};
-          if (in[e]) {
-            const int64_t o = elem(A, false, a);
-            dv2 q = qv[e];
-            r = rv[e];
-            q.x += pick4(ce, st);
-            q.y += pick4(cd, st);
-            r.x -= al0 * q.x;
-            r.y -= al1 * q.y;
-            st_s(G.Rr + o, r);
-            rr0 += r.x * r.x;
-            rr1 += r.y * r.y;
-          }
-          if (NT > 0 && pc) {
-            ft_step<NT>(f[e], r.x, r.y, acc);
-            if (yfold) {
+          for (int e = 0; e < kGS; ++e) {
+            const int st = kGS * h + e;
+            const int64_t a = ar[e];
+            double ry = 0.0;
+            if (iny[e]) {
+              const double qy = qyv[e] + pick4(cy, st);
+              ry = ryv[e] - aly * qy;
+              G.Rr[a] = ry;
+              rry += ry * ry;
+            }
+            dv2 r = {0.0, 0.0};
+            if (in[e]) {
+              const int64_t o = elem(A, false, a);
+              dv2 q = qv[e];
+              r = rv[e];
+              q.x += pick4(ce, st);
+              q.y += pick4(cd, st);
+              r.x -= al0 * q.x;
+              r.y -= al1 * q.y;
+              st_s(G.Rr + o, r);
+              rr0 += r.x * r.x;
+              rr1 += r.y * r.y;
+            }
+            if (NT > 0 && pc && kNz) {
+              ft_step<NT>(f[e], r.x, r.y, acc);
+              if (yfold) {
 #pragma unroll
-              for (int mt = 0; mt < NT; ++mt)
-                acc_y[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[e][mt], ry, acc_y[mt], 0, 0, 0);
+                for (int mt = 0; mt < NT; ++mt)
+                  acc_y[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[e][mt], ry, acc_y[mt], 0, 0, 0);
+              }
             }
           }
         }
@@ -1212,7 +1265,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NI <= 32 ? 3
   const bool lr = NI > 0 && A.lowrank_op;
   const bool pc = NI > 0 && A.use_pc;
   // matrix-core launches have no column-0 blocks: slab 0 also owns column 0
-  const bool yfold = FW == 1 && !ycol && blockIdx.y == 0;
+  const bool yfold = FW > 0 && !ycol && blockIdx.y == 0;
   if ((int)threadIdx.x < (ycol ? 1 : (yfold ? kSC : kSlab))) {
     const int cl = threadIdx.x;
     const int rc = col_of(A, ycol, cl);
@@ -1293,81 +1346,85 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NI <= 32 ? 3
   d4 acc[NT > 0 ? NT : 1][2];
 #pragma unroll
   for (int mt = 0; mt < (NT > 0 ? NT : 1); ++mt) acc[mt][0] = acc[mt][1] = d4{0.0, 0.0, 0.0, 0.0};
-  if (FW == 1 && __any(xa || (xay && jl == 0))) {
+  if (FW > 0 && __any(xa || (xay && jl == 0))) {
     // F u per 16-row wavefront tile on the matrix cores
     constexpr int NS = (NI + 3) / 4;
     const int g = lane_id() >> 4;
     const int64_t nst = tile_steps(A);
-    for (int64_t k = 0; k < nst; ++k) {
-      const int64_t base = wave_base(A, k);
-      if (base >= A.n) break;                       // uniform over the wavefront
-      d4 ue = {0.0, 0.0, 0.0, 0.0}, ud = {0.0, 0.0, 0.0, 0.0}, uy = {0.0, 0.0, 0.0, 0.0};
-      if (NS > 0 && pc) fw_tile_y<NS>(G.F, A.n1, A.n, base, s_u, yfold, ue, ud, uy);
-      // row-steps in pairs: both steps' loads are issued before either
-      // step's stores (the compiler cannot reorder them itself, not knowing
-      // that the rows differ), then the arithmetic in row-step order
 #pragma unroll
-      for (int h = 0; h < 4 / kGS; ++h) {
-        int64_t ar[kGS];
-        bool in[kGS], iny[kGS];
-        dv2 rv[kGS], pv[kGS], xv[kGS];
-        double pyv[kGS], xyv[kGS], ryv[kGS];
-        double f[kGS][NT > 0 ? NT : 1];
+    for (int pass = FW == 2 ? 0 : 1; pass < 2; ++pass) {
+      const bool kNz = pass == 1;                   // the tiles hold bump values
+      Sweep<FW> sw;
+      int64_t base;
+      while (sw.next(A, nst, kNz, base)) {
+        d4 ue = {0.0, 0.0, 0.0, 0.0}, ud = {0.0, 0.0, 0.0, 0.0}, uy = {0.0, 0.0, 0.0, 0.0};
+        if (NS > 0 && pc && kNz) fw_tile_y<NS>(G.F, A.n1, A.n, base, s_u, yfold, ue, ud, uy);
+        // row-steps in pairs: both steps' loads are issued before either
+        // step's stores (the compiler cannot reorder them itself, not knowing
+        // that the rows differ), then the arithmetic in row-step order
 #pragma unroll
-        for (int e = 0; e < kGS; ++e) {
-          const int64_t a = base + 4 * (kGS * h + e) + g;
-          ar[e] = a;
-          in[e] = a < A.n;
-          iny[e] = yfold && jl == 0 && in[e];       // column 0 of row a
-          pyv[e] = iny[e] ? G.P[a] : 0.0;
-          xyv[e] = (iny[e] && xay) ? G.X[a] : 0.0;
-          ryv[e] = (iny[e] && cy) ? G.Rr[a] : 0.0;
-          rv[e] = pv[e] = xv[e] = dv2{0.0, 0.0};
-          if (in[e]) {
-            const int64_t o = elem(A, false, a);
-            rv[e] = ld_s(G.Rr + o);
-            pv[e] = ld_s(G.P + o);
-            if (xa) xv[e] = ld_s(G.X + o);
-          }
-          if (NT > 0 && lr) load_f<NT>(A, in[e] ? a : -1, f[e]);
-        }
+        for (int h = 0; h < 4 / kGS; ++h) {
+          int64_t ar[kGS];
+          bool in[kGS], iny[kGS];
+          dv2 rv[kGS], pv[kGS], xv[kGS];
+          double pyv[kGS], xyv[kGS], ryv[kGS];
+          double f[kGS][NT > 0 ? NT : 1];
 #pragma unroll
-        for (int e = 0; e < kGS; ++e) {
-          const int st = kGS * h + e;
-          const int64_t a = ar[e];
-          double py = 0.0;
-          if (iny[e]) {
-            py = pyv[e];
-            if (xay) G.X[a] = xyv[e] + aly * py;
-            if (cy) {
-              const double zy = pc ? (ryv[e] - pick4(uy, st)) * A.inv_c : ryv[e];
-              py = zy + bey * py;
-              G.P[a] = py;
+          for (int e = 0; e < kGS; ++e) {
+            const int64_t a = base + 4 * (kGS * h + e) + g;
+            ar[e] = a;
+            in[e] = a < A.n;
+            iny[e] = yfold && jl == 0 && in[e];       // column 0 of row a
+            pyv[e] = iny[e] ? G.P[a] : 0.0;
+            xyv[e] = (iny[e] && xay) ? G.X[a] : 0.0;
+            ryv[e] = (iny[e] && cy) ? G.Rr[a] : 0.0;
+            rv[e] = pv[e] = xv[e] = dv2{0.0, 0.0};
+            if (in[e]) {
+              const int64_t o = elem(A, false, a);
+              rv[e] = ld_s(G.Rr + o);
+              pv[e] = ld_s(G.P + o);
+              if (xa) xv[e] = ld_s(G.X + o);
             }
+            if (NT > 0 && lr && kNz) load_f<NT>(A, in[e] ? a : -1, f[e]);
           }
-          dv2 p = {0.0, 0.0};
-          if (in[e]) {
-            const int64_t o = elem(A, false, a);
-            const dv2 r = rv[e];
-            p = pv[e];
-            if (xa) {
-              dv2 x = xv[e];
-              x.x += al0 * p.x;
-              x.y += al1 * p.y;
-              st_s(G.X + o, x);
-            }
-            const double z0 = pc ? (r.x - pick4(ue, st)) * A.inv_c : r.x;
-            const double z1 = pc ? (r.y - pick4(ud, st)) * A.inv_c : r.y;
-            if (c0) p.x = z0 + be0 * p.x;
-            if (c1) p.y = z1 + be1 * p.y;
-            st_s(G.P + o, p);
-          }
-          if (NT > 0 && lr) {
-            ft_step<NT>(f[e], p.x, p.y, acc);
-            if (yfold) {
 #pragma unroll
-              for (int mt = 0; mt < NT; ++mt)
-                acc_y[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[e][mt], py, acc_y[mt], 0, 0, 0);
+          for (int e = 0; e < kGS; ++e) {
+            const int st = kGS * h + e;
+            const int64_t a = ar[e];
+            double py = 0.0;
+            if (iny[e]) {
+              py = pyv[e];
+              if (xay) G.X[a] = xyv[e] + aly * py;
+              if (cy) {
+                const double zy = pc ? (ryv[e] - pick4(uy, st)) * A.inv_c : ryv[e];
+                py = zy + bey * py;
+                G.P[a] = py;
+              }
+            }
+            dv2 p = {0.0, 0.0};
+            if (in[e]) {
+              const int64_t o = elem(A, false, a);
+              const dv2 r = rv[e];
+              p = pv[e];
+              if (xa) {
+                dv2 x = xv[e];
+                x.x += al0 * p.x;
+                x.y += al1 * p.y;
+                st_s(G.X + o, x);
+              }
+              const double z0 = pc ? (r.x - pick4(ue, st)) * A.inv_c : r.x;
+              const double z1 = pc ? (r.y - pick4(ud, st)) * A.inv_c : r.y;
+              if (c0) p.x = z0 + be0 * p.x;
+              if (c1) p.y = z1 + be1 * p.y;
+              st_s(G.P + o, p);
+            }
+            if (NT > 0 && lr && kNz) {
+              ft_step<NT>(f[e], p.x, p.y, acc);
+              if (yfold) {
+#pragma unroll
+                for (int mt = 0; mt < NT; ++mt)
+                  acc_y[mt] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[e][mt], py, acc_y[mt], 0, 0, 0);
+              }
             }
           }
         }
@@ -1639,8 +1696,9 @@ struct Launch {
   int nbs, nbu, ns, R, n1;
   bool use_pc, lowrank;
   int B;
-  bool uni;     // SpMM over the 4-row union lists
+  bool uni;     // SpMM over the 16-row union lists
   bool fw;      // F w products of the update kernels on the matrix cores
+  bool fz;      // ... leaving tiles without bump values out
   bool wide;    // a slab is 4 GiB or more: 64-bit row offsets in the union SpMM
 };
 
@@ -1676,7 +1734,8 @@ void launch_iteration(hipStream_t st, const CgArgs* dA, const Launch& L, Ctx* c)
   }
   k_cg_colsum<<<dim3(L.R, 1, L.B), kSumT, 0, st>>>(dA, 0);
   SDGP_CHECK_LAUNCH();
-  if (L.fw) k_cg_update_xr<NI, 1><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
+  if (L.fz) k_cg_update_xr<NI, 2><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
+  else if (L.fw) k_cg_update_xr<NI, 1><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else k_cg_update_xr<NI, 0><<<dim3(L.nbu, L.ns + 1, L.B), kT, 0, st>>>(dA);
   SDGP_CHECK_LAUNCH();
   k_cg_colsum<<<dim3((1 + (L.use_pc ? L.n1 : 0)) * L.R, 1, L.B), kSumT, 0, st>>>(dA, 1);
@@ -1685,7 +1744,8 @@ void launch_iteration(hipStream_t st, const CgArgs* dA, const Launch& L, Ctx* c)
     k_cg_small_solve<<<dim3(L.R, 1, L.B), 64, 0, st>>>(dA);
     SDGP_CHECK_LAUNCH();
   }
-  if (L.fw) k_cg_update_p<NI, 1><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
+  if (L.fz) k_cg_update_p<NI, 2><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
+  else if (L.fw) k_cg_update_p<NI, 1><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else k_cg_update_p<NI, 0><<<dim3(L.nbu, L.ns + 1, L.B), kT, 0, st>>>(dA);
   SDGP_CHECK_LAUNCH();
   if (L.lowrank) {
@@ -2045,6 +2105,9 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     nbs = (int)std::min<int64_t>(sh.spmm_blocks > 0 ? nbs : round8((int64_t)kUnionPerCu * c->cu_count),
                                  round8((n + kUTile - 1) / kUTile));
   double* s_part = c->get<double>(S_CG_PART, (size_t)R * nbs * B);
+  const int64_t nft = (n + 15) / 16;             // 16-row tiles of F
+  // tile flags pay from two tiles per wavefront on (sweep_tiles)
+  uint8_t* fz = fw && n > (int64_t)nbu * kBlockRows ? c->get<uint8_t>(S_CG_FTILES, (size_t)nft * B) : nullptr;
   double* ha = c->get<double>(S_CG_HIST_A, (size_t)max_iter * R * B);
   double* hb = c->get<double>(S_CG_HIST_B, (size_t)max_iter * R * B);
   // per-member state block: doubles rz[2R], rz0[R], bnorm2[R], rr_last[R];
@@ -2071,6 +2134,7 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     A.V = V ? V + m * NV : nullptr;
     A.sched = s.sched;
     A.F = n1 > 0 ? p->F : nullptr;
+    A.fz = fz ? fz + (size_t)m * nft : nullptr;
     A.Sinv = use_pc ? p->Sinv : nullptr;
     A.n1 = n1;
     A.use_pc = use_pc ? 1 : 0;
@@ -2113,7 +2177,7 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   }
   CgArgs* dA = c->get<CgArgs>(S_CG_ARGS, B);
   SDGP_HIP(hipMemcpyAsync(dA, hA.data(), B * sizeof(CgArgs), hipMemcpyHostToDevice, c->stream));
-  Launch L{nbs, nbu, ns, R, n1, use_pc, use_lr, B, uni, fw, n * kSlab * 8 >= ((int64_t)1 << 32)};
+  Launch L{nbs, nbu, ns, R, n1, use_pc, use_lr, B, uni, fw, fz != nullptr, n * kSlab * 8 >= ((int64_t)1 << 32)};
   if (!c->in_trial) {
     c->last_shape.spmm_blocks = nbs;
     c->last_shape.update_blocks = nbu;
@@ -2127,6 +2191,10 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     const int64_t gx = ((int64_t)NV + 255) / 256;
     require(gx < 0x7fffffff, "n*R too large");
     k_cg_start<<<dim3((unsigned)gx, 1, B), 256, 0, c->stream>>>(dA, ys, s.perm, kind, seed, dense_rhs);
+    SDGP_CHECK_LAUNCH();
+  }
+  if (fz) {
+    k_cg_ftiles<<<dim3((unsigned)((nft + kT / kWave - 1) / (kT / kWave)), 1, B), kT, 0, c->stream>>>(dA, fz, nft);
     SDGP_CHECK_LAUNCH();
   }
   cg_start(NI, c->stream, dA, L);
@@ -2176,7 +2244,7 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     tail_from = E;
     L.ns = 0;
     L.uni = false;
-    L.fw = false;
+    L.fw = L.fz = false;
     hA[0].ns = 0;
     SDGP_HIP(hipMemcpyAsync(dA, hA.data(), sizeof(CgArgs), hipMemcpyHostToDevice, st));
     SDGP_HIP(hipStreamSynchronize(st));

@@ -101,7 +101,7 @@ enum Slot {
   S_POP_IVCNT, S_POP_IVPTR, S_POP_IV, S_POP_ROWNNZ, S_POP_SCAN, S_POP_ROWPTR, S_POP_COL, S_POP_VAL, S_POP_CAND,
   S_POP_GRAM, S_POP_SINV,
   // column CG (small point sets)
-  S_COL_IDX, S_COL_OFF, S_COL_VAL, S_COL_COL, S_COL_FT, S_COL_STATE,
+  S_COL_IDX, S_COL_OFF, S_COL_VAL, S_COL_COL, S_COL_FT, S_COL_STATE, S_CG_FTILES,
   S_NUM
 };
 
