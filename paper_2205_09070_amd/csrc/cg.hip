@@ -2399,15 +2399,72 @@ CgResult block_cg(Ctx* c, const Csr& Am, const Sorted& s, const double* ys, int 
                         c->use_graph, probe_rtol)[0];
 }
 
-// Plain SpMM Y = A X for row-major X, Y [n][R] with R even (16-byte rows
-// of pairs): slabs of 32 columns over grid y, 16 lanes per row.
+// Plain SpMM Y = A X for row-major X, Y [n][R], R >= 2: chunks of 32 columns
+// over grid y, 16 lanes per row and a pair of columns per lane.  kPairs: whole
+// 16-byte pairs (R even, 16-byte-aligned X and Y).  Otherwise the pairs are
+// 8-byte aligned and the last column of an odd R rides with the first chunk:
+// its products are formed by the lanes that hold the row's entries, as column 0
+// in k_cg_spmm, and places past a row's end take no part (an infinite X row
+// reaches the rows only that store an entry for it).  Bound by the gathered
+// rows' bytes through the L1s: 33 columns, 200,000 rows of about 62 entries,
+// 0.24 ms against 0.49 ms with a wavefront per row and a column per lane, which
+// leaves 31 lanes idle and issues four times the loads (128 registers; bounding
+// them for a fixed 4 wavefronts per SIMD spilled 12 and measured 0.28 ms).
 namespace {
+typedef double dv2u __attribute__((ext_vector_type(2), aligned(8)));
+
+template <int... us>
+__device__ __forceinline__ void gather16_ragged(int cj, double vj, int rem, const GL double* __restrict__ Xs,
+                                                int64_t ld, double* acc, std::integer_sequence<int, us...>) {
+  double vv[16];
+  dv2 xv[16];
+  ((vv[us] = bcast16_d<us>(vj),
+    xv[us] = *reinterpret_cast<const GL dv2u*>(Xs + (int64_t)(uint32_t)bcast16_i<us>(cj) * ld)), ...);
+  ((xv[us] = us < rem ? xv[us] : dv2{0.0, 0.0}), ...);
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    acc[2 * (u & 3)] += vv[u] * xv[u].x;
+    acc[2 * (u & 3) + 1] += vv[u] * xv[u].y;
+  }
+}
+
+// (Xy null: no last column)
+__device__ __forceinline__ void ragged_row(int64_t k0, int64_t k1, const GL int32_t* __restrict__ col,
+                                           const GL double* __restrict__ val, const GL double* __restrict__ Xs,
+                                           int64_t ld, const GL double* __restrict__ Xy, dv2& q, double& y) {
+  const int j = lane_id() & 15;
+  double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  y = 0.0;
+  bool in = k0 + j < k1;
+  int cj = in ? col[k0 + j] : 0;
+  double vj = in ? val[k0 + j] : 0.0;
+  for (int64_t kb = k0; __any(kb < k1); kb += 16) {
+    const bool inn = kb + 16 + j < k1;
+    const int cn = inn ? col[kb + 16 + j] : 0;
+    const double vn = inn ? val[kb + 16 + j] : 0.0;
+    if (Xy != nullptr && in) y += vj * Xy[(int64_t)(uint32_t)cj * ld];
+    const int rem = (int)max((int64_t)0, min(k1 - kb, (int64_t)16));
+    gather16_ragged(cj, vj, rem, Xs, ld, acc, std::make_integer_sequence<int, 16>{});
+    cj = cn;
+    vj = vn;
+    in = inn;
+  }
+  q.x = (acc[0] + acc[2]) + (acc[4] + acc[6]);
+  q.y = (acc[1] + acc[3]) + (acc[5] + acc[7]);
+  y = row16_sum(y);
+}
+
+template <bool kPairs>
 __global__ __launch_bounds__(kT) void k_spmm_slab(int64_t n, const int64_t* __restrict__ row_ptr,
                                                   const int32_t* __restrict__ col, const double* __restrict__ val,
                                                   const double* __restrict__ X, int R, double* __restrict__ Y) {
   const int lane = lane_id(), g = lane >> 4, j = lane & 15, w = threadIdx.x >> 6;
+  const int Re = R & ~1;
   const int c0 = (int)blockIdx.y * kSlab + 2 * j;
-  const int cc = c0 + 1 < R ? c0 : R - 2;   // lanes past the last column read a valid pair
+  const int cc = c0 + 1 < Re ? c0 : Re - 2;   // lanes past the last column read a valid pair
+  const bool last = !kPairs && Re < R && blockIdx.y == 0;
+  const GL int32_t* cg = (const GL int32_t*)col;
+  const GL double *vg = (const GL double*)val, *Xg = (const GL double*)X;
   const int xcd = blockIdx.x & 7;
   const int64_t bi = blockIdx.x >> 3, nbx = gridDim.x >> 3;
   const int64_t nx = (n + 7) >> 3, lo = xcd * nx, hi = min(n, lo + nx);
@@ -2416,21 +2473,26 @@ __global__ __launch_bounds__(kT) void k_spmm_slab(int64_t n, const int64_t* __re
     const bool live = a < hi;
     const int64_t k0 = live ? row_ptr[a] : 0, k1 = live ? row_ptr[a + 1] : 0;
     dv2 q;
-    double unused = 0.0;
-    slab_row<false>(k0, k1, live ? (int32_t)a : 0, (const GL int32_t*)col, (const GL double*)val,
-                    (const GL double*)(X + cc), R, nullptr, q, unused);
-    if (live && c0 + 1 < R) *reinterpret_cast<dv2*>(Y + a * R + c0) = q;
+    double y = 0.0;
+    if (kPairs) slab_row<false>(k0, k1, live ? (int32_t)a : 0, cg, vg, Xg + cc, R, nullptr, q, y);
+    else ragged_row(k0, k1, cg, vg, Xg + cc, R, last ? Xg + Re : nullptr, q, y);
+    if (live && c0 + 1 < Re) {
+      if (kPairs) *reinterpret_cast<dv2*>(Y + a * R + c0) = q;
+      else *reinterpret_cast<dv2u*>(Y + a * R + c0) = q;
+    }
+    if (last && live && j == 0) Y[a * R + Re] = y;
   }
 }
 }  // namespace
 
-void spmm_slab(Ctx* c, const Csr& A, const double* X, int R, double* Y) {
-  require(R >= 2 && R % 2 == 0, "slab SpMM needs an even column count");
+void spmm_slab(Ctx* c, const Csr& A, const double* X, int R, double* Y, bool pairs) {
+  require(R >= 2, "slab SpMM needs two columns or more");
   require(A.n <= 0x7fffffffLL, "n must fit a 32-bit column index");
   const int64_t tiles = (A.n + kTile - 1) / kTile;
   const int nb = (int)std::min<int64_t>(kMaxNbs, round8(tiles));
-  const int ns = (R + kSlab - 1) / kSlab;
-  k_spmm_slab<<<dim3(nb, ns), kT, 0, c->stream>>>(A.n, A.row_ptr, A.col, A.val, X, R, Y);
+  const int ns = (R / 2 * 2 + kSlab - 1) / kSlab;
+  if (pairs) k_spmm_slab<true><<<dim3(nb, ns), kT, 0, c->stream>>>(A.n, A.row_ptr, A.col, A.val, X, R, Y);
+  else k_spmm_slab<false><<<dim3(nb, ns), kT, 0, c->stream>>>(A.n, A.row_ptr, A.col, A.val, X, R, Y);
   SDGP_CHECK_LAUNCH();
 }
 

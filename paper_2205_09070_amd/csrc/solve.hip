@@ -72,7 +72,8 @@ struct RowSweep {
   }
 };
 
-// Plain SpMM: Y = A X (one wave per row, lanes over a 64-column chunk).
+// Plain SpMM of 35 columns and more that do not make whole 16-byte pairs: Y = A X
+// (one wave per row, lanes over a 64-column chunk).
 __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t* __restrict__ row_ptr,
                                               const int32_t* __restrict__ col, const double* __restrict__ val,
                                               const double* __restrict__ X, int R, double* __restrict__ Y) {
@@ -412,8 +413,14 @@ void spmm(Ctx* c, const Csr& A, const double* X, int R, double* Y) {
     SDGP_CHECK_LAUNCH();
     return;
   }
-  if (R % 2 == 0 && (reinterpret_cast<uintptr_t>(X) % 16) == 0 && (reinterpret_cast<uintptr_t>(Y) % 16) == 0) {
-    spmm_slab(c, A, X, R, Y);
+  // Slabs of 32 columns for whole 16-byte pairs, and for other operands of one
+  // slab (33 columns: 0.49 -> 0.24 ms at 200,000 rows in sorted order; in random
+  // order 3 / 17 / 25 / 33 columns 0.44 / 0.47 / 0.56 / 0.66 -> 0.26 / 0.43 / 0.55
+  // / 0.67).  Two slabs of unaligned pairs lose to k_spmm's one chunk of 64 in
+  // random order, where the gathers come from HBM (49 columns 1.23 against 0.87).
+  const bool pairs = R % 2 == 0 && (reinterpret_cast<uintptr_t>(X) % 16) == 0 && (reinterpret_cast<uintptr_t>(Y) % 16) == 0;
+  if (pairs || (R <= 33 && A.n <= 0x7fffffffLL)) {
+    spmm_slab(c, A, X, R, Y, pairs);
     return;
   }
   const int chunks = (R + kWave - 1) / kWave;
