@@ -170,7 +170,8 @@ sdgp_status sdgp_set_timing(sdgp_ctx* ctx, int enable);
  * CG SpMM reads, for every 16 consecutive rows of its row order, one sorted
  * list of the 16 rows' distinct columns and their values in that order, so
  * each neighbour row of P is gathered once for the 16 rows and the products
- * run on the matrix cores (lists built once per solve); "fw_mfma" (-1 default = 1, 0, 1):
+ * run on the matrix cores (lists built once per solve; the Taylor log-det's
+ * terms use them by default from 16 products of 32 probes on); "fw_mfma" (-1 default = 1, 0, 1):
  * the preconditioner / factored-operator products
  * F w of the CG update kernels per 16-row tile on the matrix cores instead
  * of per-row broadcasts; "update_blocks" (0 default: one round of the

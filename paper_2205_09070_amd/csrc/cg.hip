@@ -511,14 +511,17 @@ __device__ __forceinline__ void union_mma(const dv2* xv, double yv, const double
 // 0.196 against 0.188; batches of 32 columns at 4 / 5 / 6 wavefronts per SIMD
 // 0.203 / 0.202 / 0.215 against 0.185; values loaded one by one 0.188.
 // kWide: slabs of 4 GiB and more (64-bit row offsets).  kMode 1: slab 0 and
-// column 0 (grid y = 1); kMode 2: slabs 1.. (grid y = ns - 1).  Groups are
-// dealt to the XCDs in contiguous runs (the XCD share rounded to whole
-// groups).
+// column 0 (grid y = 1); kMode 2: slabs 1.. (grid y = ns - 1); kMode 3: a
+// Taylor term over all slabs (grid y = ns), Q = P - A P / alpha (1 / alpha in
+// inv_c) and the partials of x.q at s_part[po ..], so that a term is one pass.
+// Groups are dealt to the XCDs in contiguous runs (the XCD share rounded to
+// whole groups).
 template <int kMode, bool kWide>
-__global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __restrict__ AA) {
+__global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __restrict__ AA, int64_t po) {
   const CgArgs& A = AA[blockIdx.z];
   const Gv G = gview(A);
-  if (stopped(A)) return;
+  constexpr bool kTaylor = kMode == 3;
+  if (!kTaylor && stopped(A)) return;
   constexpr bool kY = kMode == 1;
   constexpr int kVL = 3;                          // values per lane loaded ahead (384 of a batch's at most 1024)
   __shared__ __align__(16) double tile[kT / kWave][kBE * kGR + 2];   // (+ the unused places' target)
@@ -530,7 +533,7 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
   const GL double* uval = (const GL double*)A.uval;
   const GL uint16_t* upos = (const GL uint16_t*)A.upos;
   const int lane = lane_id(), g = lane >> 4, j = lane & 15, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int s = kMode == 2 ? (int)blockIdx.y + 1 : 0;
+  const int s = kMode == 2 ? (int)blockIdx.y + 1 : (kTaylor ? (int)blockIdx.y : 0);
   const int64_t n = A.n;
   const int64_t so = A.ny + (int64_t)s * n * kSlab + 2 * j;
   const GL double* Ps = G.P + so;
@@ -609,10 +612,18 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
       if (p < hi) {
         const int64_t a = G.sched ? (int64_t)G.sched[p] : p;
         const dv2 qv = {acc[R][0], acc[R][1]};
-        st_s(Qs + a * kSlab, qv);
+        if (!kTaylor) st_s(Qs + a * kSlab, qv);
         const dv2 pv = *reinterpret_cast<const GL dv2*>(Ps + a * kSlab);
-        pq0 += pv.x * qv.x;
-        pq1 += pv.y * qv.y;
+        if (kTaylor) {                            // (read again by the next term: no streaming store)
+          const dv2 xv = ld_s(G.X + so + a * kSlab);
+          const dv2 nv2 = {pv.x - qv.x * A.inv_c, pv.y - qv.y * A.inv_c};
+          *reinterpret_cast<GL dv2*>(Qs + a * kSlab) = nv2;
+          pq0 += xv.x * nv2.x;
+          pq1 += xv.y * nv2.y;
+        } else {
+          pq0 += pv.x * qv.x;
+          pq1 += pv.y * qv.y;
+        }
       }
     }
     if (kY && (lane & 3) == 0) {
@@ -626,6 +637,11 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
   }
   double* red = tile[0];
   const double t = tile_colsum(red, pq0, pq1);
+  if (kTaylor) {
+    const double all = wave_sum(t);               // (0 in the lanes past the slab's columns)
+    if (threadIdx.x == 0) G.s_part[po + (int64_t)s * A.nbs + blockIdx.x] = all;
+    return;
+  }
   if (threadIdx.x < kSlab) {
     const int rc = 1 + s * kSlab + threadIdx.x;
     if (rc < A.R) G.s_part[(int64_t)rc * A.nbs + blockIdx.x] = t;
@@ -1712,12 +1728,12 @@ void launch_iteration(hipStream_t st, const CgArgs* dA, const Launch& L, Ctx* c)
   if (L.ns == 0) {
     k_cg_spmm<0><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA);
   } else if (L.uni) {
-    if (L.wide) k_cg_spmm_u<1, true><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA);
-    else k_cg_spmm_u<1, false><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA);
+    if (L.wide) k_cg_spmm_u<1, true><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA, 0);
+    else k_cg_spmm_u<1, false><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA, 0);
     if (L.ns > 1) {
       SDGP_CHECK_LAUNCH();
-      if (L.wide) k_cg_spmm_u<2, true><<<dim3(L.nbs, L.ns - 1, L.B), kT, 0, st>>>(dA);
-      else k_cg_spmm_u<2, false><<<dim3(L.nbs, L.ns - 1, L.B), kT, 0, st>>>(dA);
+      if (L.wide) k_cg_spmm_u<2, true><<<dim3(L.nbs, L.ns - 1, L.B), kT, 0, st>>>(dA, 0);
+      else k_cg_spmm_u<2, false><<<dim3(L.nbs, L.ns - 1, L.B), kT, 0, st>>>(dA, 0);
     }
   } else {
     k_cg_spmm<1><<<dim3(L.nbs, 1, L.B), kT, 0, st>>>(dA);
@@ -1944,6 +1960,74 @@ static int64_t max_group_nnz(Ctx* c, const Csr& A, const int32_t* sched, int64_t
   return *std::max_element(h.begin(), h.end());
 }
 
+// Union lists of the shared-gather SpMM, one set per matrix: storage per group
+// by a scan over the groups' entries, then the lists.  False when they are not
+// to be used: in automatic mode when they (14 B per entry), with the caller's
+// extra bytes, would take more than half of the free device memory (large
+// populations) or more than the context's workspace may hold; always when a
+// group's values would need more than 32-bit byte offsets.
+struct UnionLists {
+  int64_t ng = 0;
+  std::vector<int64_t> off;           // matrix m's entries begin at off[m]
+  int64_t* gv = nullptr;
+  int32_t *glen = nullptr, *ucol = nullptr;
+  uint32_t *gb = nullptr, *gend = nullptr;
+  double* uval = nullptr;
+  uint16_t* upos = nullptr;
+  void put(CgArgs& A, int m) const {
+    A.gv = gv + (size_t)m * (ng + 1);
+    A.glen = glen + (size_t)m * ng;
+    A.gend = gend + (size_t)m * ng;
+    A.gb = gb + off[m] / kBE + (ng + 1) * m;
+    A.ucol = ucol + off[m];
+    A.uval = uval + off[m];
+    A.upos = upos + off[m];
+  }
+};
+static bool build_unions(Ctx* c, const std::vector<Csr>& mats, const int32_t* sched, double extra, UnionLists& u) {
+  const int B = (int)mats.size();
+  const int64_t n = mats[0].n, ng = (n + kGR - 1) / kGR;
+  for (const Csr& A : mats) require(A.nnz >= 0, "the matrix's entry count must be known");
+  u.ng = ng;
+  u.off.assign(B + 1, 0);
+  // (a group's storage is rounded up as in k_group_nnz)
+  const int64_t pad = 6 * ng + 4;
+  for (int m = 0; m < B; ++m) u.off[m + 1] = (u.off[m] + mats[m].nnz + 3 * (mats[m].nnz / kBE) + pad + 3) & ~(int64_t)3;
+  const int64_t tot = u.off[B], slots = tot / kBE + (ng + 1) * B;
+  const double need = 14.0 * (double)tot + 4.0 * (double)slots + 24.0 * (double)(ng + 1) * B + extra;
+  size_t free_b = 0, total_b = 0;
+  bool fits = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need <= 0.5 * (double)free_b;
+  if (c->arena) fits = fits && 1.25 * need <= (double)(c->arena_cap - c->arena_used);
+  else if (c->cap_bytes > 0) fits = fits && 1.25 * need + (double)c->held_bytes <= (double)c->cap_bytes;
+  if (!fits && c->union_spmm <= 0) return false;
+  if (n >= kUnionCheckRows)
+    for (const Csr& A : mats)
+      if (max_group_nnz(c, A, sched, ng) >= ((int64_t)1 << 29)) return false;
+  int64_t* gcnt = c->get<int64_t>(S_CG_UCNT, (size_t)(ng + 1));
+  u.gv = c->get<int64_t>(S_CG_UPTR, (size_t)(ng + 1) * B);
+  u.glen = c->get<int32_t>(S_CG_ULEN, (size_t)ng * B);
+  u.gend = c->get<uint32_t>(S_CG_UEND, (size_t)ng * B);
+  u.gb = c->get<uint32_t>(S_CG_UBATCH, (size_t)slots);
+  u.ucol = c->get<int32_t>(S_CG_UCOL, (size_t)tot);
+  u.uval = c->get<double>(S_CG_UVAL, (size_t)tot);
+  u.upos = c->get<uint16_t>(S_CG_UPOS, (size_t)tot);
+  size_t tb = 0;
+  SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, gcnt, u.gv, (int)(ng + 1), c->stream));
+  void* tmp = c->get<char>(S_SORT_TMP, tb);
+  for (int m = 0; m < B; ++m) {
+    int64_t* gvm = u.gv + (size_t)m * (ng + 1);
+    k_group_nnz<<<(unsigned)((ng + 256) / 256), 256, 0, c->stream>>>(n, ng, mats[m].row_ptr, sched, gcnt);
+    SDGP_CHECK_LAUNCH();
+    SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, gcnt, gvm, (int)(ng + 1), c->stream));
+    k_group_lists<<<(unsigned)((ng + kGBW - 1) / kGBW), kGBW * kWave, 0, c->stream>>>(
+        n, ng, mats[m].row_ptr, mats[m].col, mats[m].val, sched, gvm, u.glen + (size_t)m * ng,
+        u.gend + (size_t)m * ng, u.gb + u.off[m] / kBE + (ng + 1) * m, u.ucol + u.off[m], u.uval + u.off[m],
+        u.upos + u.off[m]);
+    SDGP_CHECK_LAUNCH();
+  }
+  return true;
+}
+
 std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, const Sorted& s, const double* ys,
                                      int kind, int P, uint64_t seed, double rtol, int max_iter,
                                      const double* dense_rhs, int dense_R, bool keep_v, bool use_graph,
@@ -2045,59 +2129,14 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   double* w_red = use_pc ? c->get<double>(S_CG_WRED, (size_t)(n1 + 1) * R * B) : nullptr;
   double* p_part = use_lr ? c->get<double>(S_CG_PARTG, (size_t)n1 * R * nbu * B) : nullptr;
   double* p_red = use_lr ? c->get<double>(S_CG_GP, (size_t)n1 * R * B) : nullptr;
-  // Union lists of the shared-gather SpMM (per member): storage per group by
-  // a scan over the groups' entries, then the lists (automatic from
-  // kUnionMinRows rows: below that, building the lists costs more than the
-  // solve saves)
+  // Union lists of the shared-gather SpMM (automatic from kUnionMinRows rows:
+  // below that, building the lists costs more than the solve saves)
   bool uni = ns > 0 && (sh.union_spmm > 0 || (sh.union_spmm < 0 && n >= kUnionMinRows));
-  const int64_t ng = (n + kGR - 1) / kGR;
-  std::vector<int64_t> uoff(B + 1, 0);
-  int64_t *gv = nullptr;
-  int32_t *glen = nullptr, *ucol = nullptr;
-  uint32_t *gb = nullptr, *gend = nullptr;
-  double* uval = nullptr;
-  uint16_t* upos = nullptr;
+  UnionLists ul;
   if (uni) {
-    for (int m = 0; m < B; ++m) require(mem[m].A.nnz >= 0, "the matrix's entry count must be known");
-    // (a group's storage is rounded up as in k_group_nnz)
-    const int64_t pad = 6 * ng + 4;
-    for (int m = 0; m < B; ++m) uoff[m + 1] = (uoff[m] + mem[m].A.nnz + 3 * (mem[m].A.nnz / kBE) + pad + 3) & ~(int64_t)3;
-    const int64_t tot = uoff[B];
-    const int64_t slots = tot / kBE + (ng + 1) * B;
-    // in automatic mode the CSR SpMM is used instead when the lists (14 B per
-    // entry) would take more than half of the free device memory (large
-    // populations) or more than the context's workspace may hold
-    const double need = 14.0 * (double)tot + 4.0 * (double)slots + 24.0 * (double)(ng + 1) * B;
-    size_t free_b = 0, total_b = 0;
-    bool fits = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need <= 0.5 * (double)free_b;
-    if (c->arena) fits = fits && 1.25 * need <= (double)(c->arena_cap - c->arena_used);
-    else if (c->cap_bytes > 0) fits = fits && 1.25 * need + (double)c->held_bytes <= (double)c->cap_bytes;
-    if (!fits && c->union_spmm <= 0) uni = false;
-    if (uni && n >= kUnionCheckRows)               // a group's values need 32-bit byte offsets
-      for (int m = 0; m < B && uni; ++m) uni = max_group_nnz(c, mem[m].A, s.sched, ng) < ((int64_t)1 << 29);
-    if (uni) {
-      int64_t* gcnt = c->get<int64_t>(S_CG_UCNT, (size_t)(ng + 1));
-      gv = c->get<int64_t>(S_CG_UPTR, (size_t)(ng + 1) * B);
-      glen = c->get<int32_t>(S_CG_ULEN, (size_t)ng * B);
-      gend = c->get<uint32_t>(S_CG_UEND, (size_t)ng * B);
-      gb = c->get<uint32_t>(S_CG_UBATCH, (size_t)slots);
-      ucol = c->get<int32_t>(S_CG_UCOL, (size_t)tot);
-      uval = c->get<double>(S_CG_UVAL, (size_t)tot);
-      upos = c->get<uint16_t>(S_CG_UPOS, (size_t)tot);
-      size_t tb = 0;
-      SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, gcnt, gv, (int)(ng + 1), c->stream));
-      void* tmp = c->get<char>(S_SORT_TMP, tb);
-      for (int m = 0; m < B; ++m) {
-        int64_t* gvm = gv + (size_t)m * (ng + 1);
-        k_group_nnz<<<(unsigned)((ng + 256) / 256), 256, 0, c->stream>>>(n, ng, mem[m].A.row_ptr, s.sched, gcnt);
-        SDGP_CHECK_LAUNCH();
-        SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, gcnt, gvm, (int)(ng + 1), c->stream));
-        k_group_lists<<<(unsigned)((ng + kGBW - 1) / kGBW), kGBW * kWave, 0, c->stream>>>(
-            n, ng, mem[m].A.row_ptr, mem[m].A.col, mem[m].A.val, s.sched, gvm, glen + (size_t)m * ng,
-            gend + (size_t)m * ng, gb + uoff[m] / kBE + (ng + 1) * m, ucol + uoff[m], uval + uoff[m], upos + uoff[m]);
-        SDGP_CHECK_LAUNCH();
-      }
-    }
+    std::vector<Csr> mats(B);
+    for (int m = 0; m < B; ++m) mats[m] = mem[m].A;
+    uni = build_unions(c, mats, s.sched, 0.0, ul);
   }
   // union-list SpMM: one resident round of blocks unless a grid was chosen
   // (0.180 / 0.186 ms per launch with one / two rounds at 400,000 points)
@@ -2153,13 +2192,8 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     A.w_red = w_red ? w_red + (size_t)m * (n1 + 1) * R : nullptr;
     A.p_part = p_part ? p_part + (size_t)m * n1 * R * nbu : nullptr;
     A.p_red = p_red ? p_red + (size_t)m * n1 * R : nullptr;
-    A.gv = uni ? gv + (size_t)m * (ng + 1) : nullptr;
-    A.glen = uni ? glen + (size_t)m * ng : nullptr;
-    A.gend = uni ? gend + (size_t)m * ng : nullptr;
-    A.gb = uni ? gb + uoff[m] / kBE + (ng + 1) * m : nullptr;
-    A.ucol = uni ? ucol + uoff[m] : nullptr;
-    A.uval = uni ? uval + uoff[m] : nullptr;
-    A.upos = uni ? upos + uoff[m] : nullptr;
+    A.gv = nullptr;
+    if (uni) ul.put(A, m);
     char* mb = sb + sbytes * m;
     A.st.rz = reinterpret_cast<double*>(mb);
     A.st.rz0 = A.st.rz + 2 * (size_t)R;
@@ -2397,6 +2431,86 @@ CgResult block_cg(Ctx* c, const Csr& Am, const Sorted& s, const double* ys, int 
   mem[0].pc = pc;
   return block_cg_multi(c, mem, s, ys, kind, P, seed, rtol, max_iter, dense_rhs, dense_R, keep_v,
                         c->use_graph, probe_rtol)[0];
+}
+
+// ------------------------------------------------------------ Taylor terms
+namespace {
+// Rademacher probes of the slab layout ([slab][n][32], caller row perm[a]) into
+// Z and V; zeros in the columns past the last probe.
+__global__ __launch_bounds__(256) void k_taylor_slabs(const int32_t* __restrict__ perm, int64_t n, int P, int64_t len,
+                                                      uint64_t seed, double* __restrict__ Z, double* __restrict__ V) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= len) return;
+  const int64_t row = i / kSlab, a = row % n;
+  const int p = (int)(row / n) * kSlab + (int)(i % kSlab);
+  double z = 0.0;
+  if (p < P) z = (splitmix64_at(seed, ((uint64_t)p << 32) + (uint64_t)perm[a] + 1ull) >> 63) ? -1.0 : 1.0;
+  Z[i] = z;
+  V[i] = z;
+}
+}  // namespace
+
+// The sum over the Taylor terms on the union lists.  The merge of the lists is
+// paid back by the terms: plain products and passes -> lists, ms at 32 probes,
+// 10 / 50 terms: 65,536 points of 30 entries per row 1.01 -> 1.06 / 2.93 -> 2.22,
+// 100,000 of 100 2.11 -> 2.14 / 7.53 -> 4.75, 400,000 of 60 7.17 -> 6.86 / 28.9
+// -> 18.2, but 20,000 of 30 0.63 -> 0.69 / 1.42 -> 1.28; so from kUnionMinRows
+// rows and 16 slab products on.  The last slab is computed whole, and still wins
+// with 8 columns of it in use (400,000 points, 50 terms: 23.6 -> 18.2).
+constexpr int kTaylorProducts = 16;
+constexpr int kTaylorLast = 8;
+
+bool taylor_terms(Ctx* c, const Csr& A, const Sorted& s, int P, int terms, uint64_t seed, double alpha, double* acc) {
+  const int64_t n = A.n;
+  const int ns = (P + kSlab - 1) / kSlab;
+  const bool pays = n >= kUnionMinRows && (int64_t)ns * terms >= kTaylorProducts &&
+                    (P % kSlab == 0 || P % kSlab >= kTaylorLast);
+  if (c->union_spmm == 0 || A.nnz < 0 || (c->union_spmm < 0 && !pays)) return false;
+  const int64_t len = (int64_t)ns * n * kSlab;
+  if ((len + 255) / 256 >= 0x7fffffff) return false;
+  const int nbs = (int)std::min<int64_t>(round8((int64_t)kUnionPerCu * c->cu_count), round8((n + kUTile - 1) / kUTile));
+  const int64_t np = (int64_t)ns * nbs;           // partials of a term
+  UnionLists ul;
+  const double extra = 8.0 * (3.0 * (double)len + (double)np * terms);   // Z, V, W and the partials follow
+  if (!build_unions(c, {A}, s.sched, extra, ul)) return false;
+  double* Z = c->get<double>(S_CG_X, (size_t)len);
+  double* V = c->get<double>(S_CG_R, (size_t)len);
+  double* W = c->get<double>(S_CG_Q, (size_t)len);
+  double* part = c->get<double>(S_RED_OUT, (size_t)(np * terms));
+  CgArgs h[2] = {};
+  for (int k = 0; k < 2; ++k) {
+    CgArgs& H = h[k];
+    H.n = n;
+    H.ns = ns;
+    H.sched = s.sched;
+    H.X = Z;
+    H.P = k ? W : V;
+    H.Q = k ? V : W;
+    H.inv_c = 1.0 / alpha;
+    H.nbs = nbs;
+    H.s_part = part;
+    ul.put(H, 0);
+  }
+  CgArgs* dA = c->get<CgArgs>(S_CG_ARGS, 2);
+  SDGP_HIP(hipMemcpyAsync(dA, h, sizeof(h), hipMemcpyHostToDevice, c->stream));
+  k_taylor_slabs<<<(unsigned)((len + 255) / 256), 256, 0, c->stream>>>(s.perm, n, P, len, seed, Z, V);
+  SDGP_CHECK_LAUNCH();
+  const bool wide = n * kSlab * 8 >= ((int64_t)1 << 32);
+  for (int k = 0; k < terms; ++k) {
+    if (wide) k_cg_spmm_u<3, true><<<dim3(nbs, ns), kT, 0, c->stream>>>(dA + (k & 1), k * np);
+    else k_cg_spmm_u<3, false><<<dim3(nbs, ns), kT, 0, c->stream>>>(dA + (k & 1), k * np);
+    SDGP_CHECK_LAUNCH();
+  }
+  std::vector<double> hp((size_t)(np * terms));
+  SDGP_HIP(hipMemcpyAsync(hp.data(), part, hp.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  SDGP_HIP(hipStreamSynchronize(c->stream));
+  *acc = 0.0;
+  for (int k = 0; k < terms; ++k) {
+    double t = 0.0;
+    for (int64_t b = 0; b < np; ++b) t += hp[(size_t)(k * np + b)];
+    *acc += t / P / (k + 1);
+  }
+  return true;
 }
 
 // Plain SpMM Y = A X for row-major X, Y [n][R], R >= 2: chunks of 32 columns

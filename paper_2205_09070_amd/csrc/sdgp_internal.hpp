@@ -353,6 +353,9 @@ Precond lowrank_precond(Ctx* c, const Sorted& s, const KParams& kp, const Bumps&
 std::vector<Precond> lowrank_precond_pop(Ctx* c, const Sorted& s, const std::vector<KParams>& kp,
                                          const double* F0, std::vector<std::string>* failed);
 void spmm(Ctx* c, const Csr& A, const double* X, int R, double* Y);
+// The sum over the Taylor terms of the log-det by the union lists; false when
+// they are not taken (the caller's plain products follow).
+bool taylor_terms(Ctx* c, const Csr& A, const Sorted& s, int P, int terms, uint64_t seed, double alpha, double* acc);
 // Y = A X for row-major [n][R] blocks, R >= 2; pairs: R even, X and Y 16-byte aligned.
 void spmm_slab(Ctx* c, const Csr& A, const double* X, int R, double* Y, bool pairs);
 // Randomised Taylor-series log-det (Boutsidis et al. 2017) on A.

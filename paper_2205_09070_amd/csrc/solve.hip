@@ -367,6 +367,9 @@ double logdet_taylor(Ctx* c, const Csr& A, const Sorted& s, int P, int terms, ui
   double alpha = 0.0;
   for (double v : hm) alpha = std::max(alpha, v);
   require(alpha > 0.0 && std::isfinite(alpha), "matrix has no positive row sums");
+  *alpha_out = alpha;
+  double acc = 0.0;
+  if (taylor_terms(c, A, s, P, terms, seed, alpha, &acc)) return (double)n * std::log(alpha) - acc;
   const size_t len = (size_t)n * P;
   double* Z = c->get<double>(S_CG_X, len);
   double* V = c->get<double>(S_CG_R, len);
@@ -383,13 +386,11 @@ double logdet_taylor(Ctx* c, const Csr& A, const Sorted& s, int P, int terms, ui
   }
   SDGP_HIP(hipMemcpyAsync(hp.data(), part, hp.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   SDGP_HIP(hipStreamSynchronize(c->stream));
-  double acc = 0.0;
   for (int k = 1; k <= terms; ++k) {
     double t = 0.0;
     for (int b = 0; b < nb; ++b) t += hp[(size_t)(k - 1) * nb + b];
     acc += t / P / k;
   }
-  *alpha_out = alpha;
   return (double)n * std::log(alpha) - acc;
 }
 
