@@ -61,7 +61,7 @@ struct CgState {
   int32_t* iters;   // [R]
   int32_t* done;    // [1] executed iterations once every column stopped
   int32_t* not_spd; // [1]
-  int32_t* it;      // [1] iteration counter (advanced by k_cg_check)
+  int32_t* it;      // [1] iteration counter (advanced by check_stop)
   double* hist_a;   // [max_iter][R]
   double* hist_b;   // [max_iter][R]
 };
@@ -88,7 +88,7 @@ struct CgArgs {
   double* s_part;             // [R][nbs] p.(A p) partials of the SpMM
   double* s_red;              // [R]
   double* u_part;             // [(1+n1) R][nbu]: r.r, then F^T r (row R + i R + c)
-  double* u_red;              // [(1+n1) R]
+  double* u_red;              // [R] r.r
   double* w_red;              // [(n1+1) R]: u = S^{-1} g (row i R + c), then g.u (row n1 R + c)
   double* p_part;             // [n1 R][nbu] F^T p (row i R + c)
   double* p_red;              // [n1 R]
@@ -655,23 +655,50 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
   }
 }
 
+// Records the executed iteration count in done when no column is active
+// and advances the iteration counter (one block per member).
+__device__ __forceinline__ void check_stop(const CgArgs& A) {
+  const int it = *A.st.it;
+  const int nxt = (it & 1) ^ 1;
+  __shared__ int left;
+  if (threadIdx.x == 0) left = 0;
+  __syncthreads();
+  int mine = 0;
+  for (int r = threadIdx.x; r < A.R; r += blockDim.x) mine |= A.st.act[nxt * A.R + r];
+  if (mine) atomicOr(&left, 1);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (!left) *A.st.done = it + 1;
+    *A.st.it = it + 1;
+  }
+}
+
 // out[c] = sum_b part[c][b] in a fixed order (one 1024-thread block per
-// column).  which: 0 SpMM partials, 1 update partials (r.r and F^T r),
-// 2 F^T p partials.
+// column).  which: 0 SpMM partials, 1 r.r partials, 2 F^T p partials, and in
+// the block past the last column the end of the iteration (3: that alone; the
+// other blocks may see the counters before or after: past the last iteration
+// nobody reads their sums).  A latency chain of a launch, a load and a
+// reduction: sums over wavefronts by DPP rather than 10 rounds through LDS, and
+// one launch where there were two (with k_cg_coef, 20,000 points in 3-D, 16
+// probes and 8 bumps: 59 -> 53 us per iteration, of which the
+// update grid without empty blocks is a part; 16 members: 113 -> 95 ms a call).
 constexpr int kSumT = 1024;
 __global__ __launch_bounds__(kSumT) void k_cg_colsum(const CgArgs* __restrict__ AA, int which) {
   const CgArgs& A = AA[blockIdx.z];
   if (stopped(A)) return;
   const Gv G = gview(A);
-  __shared__ double red[kSumT];
+  __shared__ double red[kSumT / kWave];
   const GL double* part;
   double* out;
   int nparts, ncols;
   if (which == 0) { part = G.s_part; out = A.s_red; nparts = A.nbs; ncols = A.R; }
-  else if (which == 1) { part = G.u_part; out = A.u_red; nparts = A.nbu; ncols = (1 + (A.use_pc ? A.n1 : 0)) * A.R; }
-  else { part = G.p_part; out = A.p_red; nparts = A.nbu; ncols = A.n1 * A.R; }
+  else if (which == 1) { part = G.u_part; out = A.u_red; nparts = A.nbu; ncols = A.R; }
+  else { part = G.p_part; out = A.p_red; nparts = A.nbu; ncols = which == 2 ? A.n1 * A.R : 0; }
   const int c = blockIdx.x;
-  if (c >= ncols) return;
+  if (c >= ncols) {                                // uniform over the block
+    if (which >= 2) check_stop(A);
+    return;
+  }
   const GL double* pc = part + (int64_t)c * nparts;
   double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
   int b = threadIdx.x;
@@ -682,38 +709,56 @@ __global__ __launch_bounds__(kSumT) void k_cg_colsum(const CgArgs* __restrict__ 
     v3 += pc[b + 3 * kSumT];
   }
   for (; b < nparts; b += kSumT) v0 += pc[b];
-  red[threadIdx.x] = (v0 + v1) + (v2 + v3);
+  const double v = wave_sum((v0 + v1) + (v2 + v3));
+  if (lane_id() == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int o = kSumT / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
+  if (threadIdx.x < kWave) {
+    const double t = wave_sum(threadIdx.x < kSumT / kWave ? red[threadIdx.x] : 0.0);
+    if (threadIdx.x == 0) out[c] = t;
   }
-  if (threadIdx.x == 0) out[c] = red[0];
 }
 
-// Preconditioner coefficients per column (one 64-thread block per column):
-// u = S^{-1} g with g = F^T r from u_red, and g.u, each sum in a fixed order.
-__global__ __launch_bounds__(64) void k_cg_small_solve(const CgArgs* __restrict__ AA) {
+// Preconditioner coefficients, one block per column: r.r and g = F^T r from
+// their partials (a wavefront per row of partials), then u = S^{-1} g and g.u,
+// each sum in a fixed order.
+__global__ __launch_bounds__(kSumT) void k_cg_coef(const CgArgs* __restrict__ AA) {
   const CgArgs& A = AA[blockIdx.z];
   if (stopped(A)) return;
   const int rc = blockIdx.x;
   if (rc >= A.R) return;
-  __shared__ double gs[64];
+  const Gv G = gview(A);
+  __shared__ double gs[1 + 64];
   __shared__ double gu[64];
-  const int i = threadIdx.x;
-  const int n1 = A.n1;
-  gs[i] = i < n1 ? A.u_red[(int64_t)A.R + (int64_t)i * A.R + rc] : 0.0;
+  const int n1 = A.n1, lane = lane_id();
+  for (int row = threadIdx.x >> 6; row <= n1; row += kSumT / kWave) {
+    const GL double* pc = G.u_part + ((int64_t)row * A.R + rc) * A.nbu;
+    double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
+    int b = lane;
+    for (; b + 3 * kWave < A.nbu; b += 4 * kWave) {
+      v0 += pc[b];
+      v1 += pc[b + kWave];
+      v2 += pc[b + 2 * kWave];
+      v3 += pc[b + 3 * kWave];
+    }
+    for (; b < A.nbu; b += kWave) v0 += pc[b];
+    const double v = wave_sum((v0 + v1) + (v2 + v3));
+    if (lane == 0) gs[row] = v;
+  }
   __syncthreads();
-  double u = 0.0;
-  if (i < n1)
-    for (int k = 0; k < n1; ++k) u += A.Sinv[i * n1 + k] * gs[k];
-  if (i < n1) A.w_red[(int64_t)i * A.R + rc] = u;
-  gu[i] = i < n1 ? gs[i] * u : 0.0;
+  const int i = threadIdx.x;
+  if (i < 64) {
+    double u = 0.0;
+    if (i < n1)
+      for (int k = 0; k < n1; ++k) u += A.Sinv[i * n1 + k] * gs[1 + k];
+    if (i < n1) A.w_red[(int64_t)i * A.R + rc] = u;
+    gu[i] = i < n1 ? gs[1 + i] * u : 0.0;
+  }
   __syncthreads();
   if (i == 0) {
     double t = 0.0;
     for (int k = 0; k < n1; ++k) t += gu[k];
     A.w_red[(int64_t)n1 * A.R + rc] = t;
+    A.u_red[rc] = gs[0];
   }
 }
 
@@ -1008,7 +1053,7 @@ __device__ __forceinline__ int64_t elem(const CgArgs& A, bool ycol, int64_t a) {
   return ycol ? a : A.ny + (int64_t)blockIdx.y * A.n * kSlab + a * kSlab + 2 * (lane_id() & 15);
 }
 
-// u = S^{-1} g of column rc (from k_cg_small_solve) into us[i * kSC]
+// u = S^{-1} g of column rc (from k_cg_coef) into us[i * kSC]
 // (stride kSlab); returns g.u.
 template <int NI>
 __device__ __forceinline__ double coef_u(const CgArgs& A, int rc, double* us) {
@@ -1480,27 +1525,6 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NI <= 32 ? 3
   if (yfold && NT > 0 && lr) put_yfold_partials<(NT > 0 ? NT : 1)>(A, red, false, 0.0, 0, true, acc_y, G.p_part, 0);
 }
 
-// Records the executed iteration count in done when no column is active
-// and advances the iteration counter (one block per member).
-__global__ void k_cg_check(const CgArgs* __restrict__ AA) {
-  const CgArgs& A = AA[blockIdx.z];
-  const Gv G = gview(A);
-  if (stopped(A)) return;
-  const int it = *A.st.it;
-  const int nxt = (it & 1) ^ 1;
-  __shared__ int left;
-  if (threadIdx.x == 0) left = 0;
-  __syncthreads();
-  int mine = 0;
-  for (int r = threadIdx.x; r < A.R; r += blockDim.x) mine |= A.st.act[nxt * A.R + r];
-  if (mine) atomicOr(&left, 1);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (!left) *A.st.done = it + 1;
-    *A.st.it = it + 1;
-  }
-}
-
 // ------------------------------------------------------------ start
 // x = 0, r = b, p = 0 over the whole slab layout (padding included).
 // Column 0 is y (or the first dense column); probe p (column 1+p) is the
@@ -1754,21 +1778,15 @@ void launch_iteration(hipStream_t st, const CgArgs* dA, const Launch& L, Ctx* c)
   else if (L.fw) k_cg_update_xr<NI, 1><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else k_cg_update_xr<NI, 0><<<dim3(L.nbu, L.ns + 1, L.B), kT, 0, st>>>(dA);
   SDGP_CHECK_LAUNCH();
-  k_cg_colsum<<<dim3((1 + (L.use_pc ? L.n1 : 0)) * L.R, 1, L.B), kSumT, 0, st>>>(dA, 1);
+  if (L.use_pc) k_cg_coef<<<dim3(L.R, 1, L.B), kSumT, 0, st>>>(dA);
+  else k_cg_colsum<<<dim3(L.R, 1, L.B), kSumT, 0, st>>>(dA, 1);
   SDGP_CHECK_LAUNCH();
-  if (L.use_pc) {
-    k_cg_small_solve<<<dim3(L.R, 1, L.B), 64, 0, st>>>(dA);
-    SDGP_CHECK_LAUNCH();
-  }
   if (L.fz) k_cg_update_p<NI, 2><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else if (L.fw) k_cg_update_p<NI, 1><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else k_cg_update_p<NI, 0><<<dim3(L.nbu, L.ns + 1, L.B), kT, 0, st>>>(dA);
   SDGP_CHECK_LAUNCH();
-  if (L.lowrank) {
-    k_cg_colsum<<<dim3(L.n1 * L.R, 1, L.B), kSumT, 0, st>>>(dA, 2);
-    SDGP_CHECK_LAUNCH();
-  }
-  k_cg_check<<<dim3(1, 1, L.B), 256, 0, st>>>(dA);
+  if (L.lowrank) k_cg_colsum<<<dim3(L.n1 * L.R + 1, 1, L.B), kSumT, 0, st>>>(dA, 2);
+  else k_cg_colsum<<<dim3(1, 1, L.B), kSumT, 0, st>>>(dA, 3);
   SDGP_CHECK_LAUNCH();
 }
 
@@ -1776,12 +1794,9 @@ template <int NI>
 void launch_start(hipStream_t st, const CgArgs* dA, const Launch& L) {
   k_cg_norm<NI><<<dim3(L.nbu, L.ns + 1, L.B), kT, 0, st>>>(dA);
   SDGP_CHECK_LAUNCH();
-  k_cg_colsum<<<dim3((1 + (L.use_pc ? L.n1 : 0)) * L.R, 1, L.B), kSumT, 0, st>>>(dA, 1);
+  if (L.use_pc) k_cg_coef<<<dim3(L.R, 1, L.B), kSumT, 0, st>>>(dA);
+  else k_cg_colsum<<<dim3(L.R, 1, L.B), kSumT, 0, st>>>(dA, 1);
   SDGP_CHECK_LAUNCH();
-  if (L.use_pc) {
-    k_cg_small_solve<<<dim3(L.R, 1, L.B), 64, 0, st>>>(dA);
-    SDGP_CHECK_LAUNCH();
-  }
   k_cg_init_fin<NI><<<dim3(L.nbu, L.ns + 1, L.B), kT, 0, st>>>(dA);
   SDGP_CHECK_LAUNCH();
   if (L.lowrank) {
@@ -1830,6 +1845,14 @@ int update_blocks_per_cu(int NI, bool fw) {
     case 32: return update_blocks_per_cu<32>(fw);
     default: return update_blocks_per_cu<64>(fw);
   }
+}
+
+// Blocks of the update kernels with rows to do: 64 rows each on the matrix
+// cores, 16 with broadcasts (a block without rows still writes its partials,
+// and every later sum reads them).
+int64_t update_tiles(int64_t n, bool fw) {
+  const int64_t rows = fw ? kBlockRows : kTile;
+  return round8((n + rows - 1) / rows);
 }
 
 // ------------------------------------------------------------ autotuner
@@ -1900,7 +1923,8 @@ static TuneChoice run_tuner(Ctx* c, const std::vector<CgMember>& mem, const Sort
   best.spmm_blocks = spmm_grids(best.union_spmm)[0];
   best.fw_mfma = (ns > 0 && n1 > 0) ? 1 : 0;
   const int round1 = update_blocks_per_cu(NI, best.fw_mfma != 0) * c->cu_count;
-  best.update_blocks = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)kMaxNbu, (int64_t)round1, round8(tiles)}));
+  best.update_blocks = (int)std::max<int64_t>(
+      1, std::min<int64_t>({(int64_t)kMaxNbu, (int64_t)round1, update_tiles(n, best.fw_mfma != 0)}));
   double t_best = trial(best);
   best.default_ms_per_iter = t_best;
   best.ms_per_iter = t_best;
@@ -1937,7 +1961,7 @@ static TuneChoice run_tuner(Ctx* c, const std::vector<CgMember>& mem, const Sort
     for (int f : fws) {
       const int r1 = update_blocks_per_cu(NI, f != 0) * c->cu_count;
       for (int k = 1; k <= 3; ++k) {
-        const int ub = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)k * r1, (int64_t)65535, round8(tiles)}));
+        const int ub = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)k * r1, (int64_t)65535, update_tiles(n, f != 0)}));
         if (f == base.fw_mfma && ub == base.update_blocks) continue;
         TuneChoice cand = base;
         cand.fw_mfma = f;
@@ -2115,7 +2139,8 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   const bool fw = ns > 0 && n1 > 0 && sh.fw_mfma != 0;
   const int64_t nbu_cap = sh.update_blocks > 0
                               ? sh.update_blocks
-                              : std::min<int64_t>(kMaxNbu, (int64_t)update_blocks_per_cu(NI, fw) * c->cu_count);
+                              : std::min<int64_t>({(int64_t)kMaxNbu, update_tiles(n, fw),
+                                                   (int64_t)update_blocks_per_cu(NI, fw) * c->cu_count});
   const int nbu = (int)std::max<int64_t>(1, std::min<int64_t>(nbu_cap, round8(tiles)));
   const int nu = 1 + (use_pc ? n1 : 0);
   double* X = c->get<double>(S_CG_X, NV * B);
@@ -2125,7 +2150,7 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   double* V = (use_pc && keep_v) ? c->get<double>(S_CG_V, NV * B) : nullptr;
   double* s_red = c->get<double>(S_CG_SRED, (size_t)R * B);
   double* u_part = c->get<double>(S_CG_PART2, (size_t)nu * R * nbu * B);
-  double* u_red = c->get<double>(S_CG_G, (size_t)nu * R * B);
+  double* u_red = c->get<double>(S_CG_G, (size_t)R * B);
   double* w_red = use_pc ? c->get<double>(S_CG_WRED, (size_t)(n1 + 1) * R * B) : nullptr;
   double* p_part = use_lr ? c->get<double>(S_CG_PARTG, (size_t)n1 * R * nbu * B) : nullptr;
   double* p_red = use_lr ? c->get<double>(S_CG_GP, (size_t)n1 * R * B) : nullptr;
@@ -2188,7 +2213,7 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     A.s_part = s_part + (size_t)m * R * nbs;
     A.s_red = s_red + (size_t)m * R;
     A.u_part = u_part + (size_t)m * nu * R * nbu;
-    A.u_red = u_red + (size_t)m * nu * R;
+    A.u_red = u_red + (size_t)m * R;
     A.w_red = w_red ? w_red + (size_t)m * (n1 + 1) * R : nullptr;
     A.p_part = p_part ? p_part + (size_t)m * n1 * R * nbu : nullptr;
     A.p_red = p_red ? p_red + (size_t)m * n1 * R : nullptr;
