@@ -256,7 +256,9 @@ sdgp_status sdgp_kernel_nnz(sdgp_ctx* ctx, const sdgp_kernel_desc* desc, const d
     require(desc && x && nnz_out, "NULL argument");
     validate(*desc, h, n);
     Sorted s = order_points(ctx, x, n, desc->dim, h[1], false);
-    Assembled as = assemble_all(ctx, s, *desc, h, true, nullptr);
+    // the count alone: with no room for entries the fill is left out
+    const CsrOut out{ctx->get<int64_t>(S_ROW_PTR, n + 1), nullptr, nullptr, -1};
+    Assembled as = assemble_all(ctx, s, *desc, h, true, nullptr, false, &out);
     *nnz_out = as.A.nnz;
   });
 }
