@@ -63,7 +63,8 @@ sdgp_status guarded(sdgp_ctx* ctx, F&& f) {
   if (!ctx) return SDGP_ERR_INVALID_ARG;
   try {
     SDGP_HIP(hipSetDevice(ctx->device));
-    ctx->ev_used = 0;
+    ctx->ev_used = 0;          // the pool's events serve this call anew,
+    ctx->spmm_events.clear();  // so the last call's launches are forgotten with them
     f();
     ctx->err.clear();
     return SDGP_OK;
