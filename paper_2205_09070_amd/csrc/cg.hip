@@ -656,8 +656,10 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
 }
 
 // Records the executed iteration count in done when no column is active
-// and advances the iteration counter (one block per member).
+// and advances the iteration counter (one block per member; its barriers
+// stand between its wavefronts' reads of the counters and the writes).
 __device__ __forceinline__ void check_stop(const CgArgs& A) {
+  if (stopped(A)) return;
   const int it = *A.st.it;
   const int nxt = (it & 1) ^ 1;
   __shared__ int left;
@@ -675,9 +677,10 @@ __device__ __forceinline__ void check_stop(const CgArgs& A) {
 
 // out[c] = sum_b part[c][b] in a fixed order (one 1024-thread block per
 // column).  which: 0 SpMM partials, 1 r.r partials, 2 F^T p partials, and in
-// the block past the last column the end of the iteration (3: that alone; the
-// other blocks may see the counters before or after: past the last iteration
-// nobody reads their sums).  A latency chain of a launch, a load and a
+// the block past the last column the end of the iteration (3: that alone).
+// That block writes the counters, so the others of its launch leave them alone:
+// they sum in any case, which past the last iteration changes nothing (the
+// partials are those of the last one).  A latency chain of a launch, a load and a
 // reduction: sums over wavefronts by DPP rather than 10 rounds through LDS, and
 // one launch where there were two (with k_cg_coef, 20,000 points in 3-D, 16
 // probes and 8 bumps: 59 -> 53 us per iteration, of which the
@@ -685,7 +688,7 @@ __device__ __forceinline__ void check_stop(const CgArgs& A) {
 constexpr int kSumT = 1024;
 __global__ __launch_bounds__(kSumT) void k_cg_colsum(const CgArgs* __restrict__ AA, int which) {
   const CgArgs& A = AA[blockIdx.z];
-  if (stopped(A)) return;
+  if (which < 2 && stopped(A)) return;
   const Gv G = gview(A);
   __shared__ double red[kSumT / kWave];
   const GL double* part;

@@ -237,9 +237,12 @@ struct Pool {
     for (int i = 1; i < n; ++i) threads.emplace_back([this, i] { loop(i); });
   }
   void work(int i) {
+    // EMU_ORDER=down: the blocks of a launch from the last to the first
+    static const bool down = std::getenv("EMU_ORDER") != nullptr && std::strcmp(std::getenv("EMU_ORDER"), "down") == 0;
     for (;;) {
-      const int64_t b = next.fetch_add(1);
-      if (b >= total) break;
+      const int64_t k = next.fetch_add(1);
+      if (k >= total) break;
+      const int64_t b = down ? total - 1 - k : k;
       const dim3 bid((unsigned)(b % grid.x), (unsigned)((b / grid.x) % grid.y), (unsigned)(b / ((int64_t)grid.x * grid.y)));
       run_block(*workers[i], *body, bid, block, grid, name);
     }

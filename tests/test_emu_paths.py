@@ -29,3 +29,24 @@ def test_path(emu_lib, case):
     print(r.stdout[-4000:])
     print(r.stderr[-6000:])
     assert r.returncode == 0 and "case %s holds" % case in r.stdout
+
+
+@pytest.mark.parametrize("order", ["up", "down"])
+def test_sums_do_not_depend_on_block_order(emu_lib, order, tmp_path):
+    """k_cg_colsum's blocks run in any order: the one that ends the iteration
+    may come first, and every sum of the launch is written all the same."""
+    from tests.emu import build_emu
+    src = emu_lib + ".src"
+    emu = os.path.join(ROOT, "tests", "emu")
+    exe = str(tmp_path / "colsum")
+    objs = sorted(os.path.join(src, f) for f in os.listdir(src) if f.endswith(".o") and f != "cg.cpp.o")
+    r = subprocess.run([build_emu.CLANG, "-std=c++17", "-O1", "-g", "-fsanitize=address", "-fno-omit-frame-pointer",
+                        "-Wno-everything", "-I", os.path.join(emu, "include"), "-I", emu, "-I", src, "-I",
+                        os.path.join(ROOT, "include"), os.path.join(emu, "colsum.cpp")] + objs
+                       + ["-lpthread", "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    env = dict(os.environ, EMU_ORDER=order, EMU_THREADS="1", ASAN_OPTIONS="detect_leaks=0")
+    r = subprocess.run([exe], env=env, capture_output=True, text=True, timeout=300)
+    print(r.stdout[-2000:])
+    print(r.stderr[-4000:])
+    assert r.returncode == 0
