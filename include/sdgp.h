@@ -198,8 +198,8 @@ sdgp_status sdgp_set_timing(sdgp_ctx* ctx, int enable);
  * Small point sets (up to 10048 points, by a rule on points, entries and
  * columns) are solved without the block CG: one workgroup per few columns
  * runs their whole solve in one launch.  The launch-shape options and "graph"
- * do not apply there; setting any launch-shape option, or "autotune" 2, takes
- * the block CG at every size.
+ * do not apply there; setting any launch-shape option, "autotune" 2 or a
+ * "workspace_cap" takes the block CG at every size.
  * "timing" and "graph" leave the results bitwise unchanged;
  * "union_spmm", "fw_mfma", "update_blocks" and "spmm_blocks" change only the
  * order of floating-point sums

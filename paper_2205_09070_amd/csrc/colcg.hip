@@ -639,15 +639,20 @@ bool column_cg_applies(const Ctx* c, int64_t n, int64_t nnz, int R, int B, int n
   const double col_us = (double)((groups + cu - 1) / cu) * (2.5 + (10.0 * nnz + 32.0 * n1 * n) / rate);
   const double block_us = 40.0 + ns * (256.0 * nnz / 15e6 + 2048.0 * n / 4e6);
   if (col_us > block_us) return false;
-  // workspace limits: the block CG, whose needs differ, where this one's do not fit
-  if (c->arena || c->cap_bytes > 0) {
-    const int64_t npad = (n + 63) / 64 * 64;
-    const double need = 8.0 * R * ((keep_v ? 2.0 : 1.0) * n + npad) + 2560.0 * max_steps(n, nnz) + 8.0 * n1 * npad +
-                        16.0 * max_iter * R + 9.0 * npad + 32.0 * R + 4096.0;
-    const double room = c->arena ? (double)(c->arena_cap - c->arena_used) : (double)c->cap_bytes - (double)c->held_bytes;
-    if (1.125 * need * B > room) return false;
-  }
-  return true;
+  // Limited workspace.  A context under a cap keeps to the block CG: the column
+  // CG holds buffers of its own (the matrix in slices) beside those that the
+  // block CG needs for other sizes, and what fitted the cap without it has to fit
+  // in any order of calls.  The static workspace starts empty at every call, so
+  // there the sizes decide: column CG where it leaves half of the room to the
+  // quadrature and the adjoint, or takes no more than the block CG's vectors and
+  // coefficients.
+  if (!c->arena) return c->cap_bytes == 0;
+  const int64_t npad = (n + 63) / 64 * 64;
+  const double hist = 16.0 * max_iter * R;
+  const double need = 8.0 * R * ((keep_v ? 2.0 : 1.0) * n + npad) + 2560.0 * max_steps(n, nnz) + 8.0 * n1 * npad +
+                      hist + 9.0 * npad + 32.0 * R + 4096.0;
+  const double block_need = 8.0 * (keep_v ? 5.0 : 4.0) * (n + 32.0 * ns * n) + hist;
+  return 2.25 * need * B <= (double)(c->arena_cap - c->arena_used) || need <= block_need;
 }
 
 std::vector<CgResult> column_cg(Ctx* c, const std::vector<CgMember>& mem, const Sorted& s, const double* ys, int kind,

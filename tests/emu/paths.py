@@ -34,6 +34,51 @@ def case_timing(lib):
     assert col.spmm_launches == 0 and col.spmm_ms == 0.0
 
 
+def _eval(c, w, est):
+    """(value, gradient, last shape) of one evaluation, None for OOM."""
+    try:
+        v, g, _ = c.lml_grad(w.desc, w.x, w.y, w.h, est)
+    except _lib.SdgpError as e:
+        assert e.status == _lib.OOM, e
+        return None
+    return v, g, [c.get_option(k) for k in ("last_spmm_blocks", "last_update_blocks", "last_union_spmm")]
+
+
+def _least_cap(lib, w, est, step=1.05):
+    """The least workspace_cap (to the step) that one evaluation fits in."""
+    cap = 1 << 15
+    while True:
+        c = EmuContext(lib)
+        c.set_option("workspace_cap", cap)
+        ok = _eval(c, w, est) is not None
+        c.close()
+        if ok:
+            return cap
+        cap = int(cap * step)
+
+
+def case_cap(lib):
+    """Under a workspace_cap a call that fits once fits again, with the same
+    solver and bits, and whatever smaller calls came before it."""
+    est = _lib.estimator(probes=4, seed=3, cg_rtol=1e-2, cg_max_iter=400, precond=1)
+    w, s = small(n=130), small(n=70, seed=12)
+    least = _least_cap(lib, w, est)
+    print("least cap %d" % least)
+    for f in (1.0, 1.2, 1.4, 1.7, 2.0, 3.0):
+        cap = int(least * f)
+        c = EmuContext(lib)
+        c.set_option("workspace_cap", cap)
+        a, b = _eval(c, w, est), _eval(c, w, est)
+        print("cap %d: %s, again %s" % (cap, a and a[2], b and b[2]))
+        assert a is not None and b is not None
+        assert a[2] == b[2] and a[0] == b[0] and (a[1] == b[1]).all()
+        c.close()
+        c = EmuContext(lib)
+        c.set_option("workspace_cap", cap)
+        assert _eval(c, s, est) is not None and _eval(c, w, est) is not None, "after a smaller call"
+        c.close()
+
+
 if __name__ == "__main__":
     globals()["case_" + sys.argv[2]](sys.argv[1])
     print("case %s holds" % sys.argv[2], flush=True)
