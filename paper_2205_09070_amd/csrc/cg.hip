@@ -1989,10 +1989,10 @@ static int64_t max_group_nnz(Ctx* c, const Csr& A, const int32_t* sched, int64_t
 
 // Union lists of the shared-gather SpMM, one set per matrix: storage per group
 // by a scan over the groups' entries, then the lists.  False when they are not
-// to be used: in automatic mode when they (14 B per entry), with the caller's
-// extra bytes, would take more than half of the free device memory (large
-// populations) or more than the context's workspace may hold; always when a
-// group's values would need more than 32-bit byte offsets.
+// to be used: in automatic mode when what they (14 B per entry) and the caller's
+// extra bytes add to the workspace is more than half of the free device memory
+// (large populations) or more than the context's workspace may grow by; always
+// when a group's values would need more than 32-bit byte offsets.
 struct UnionLists {
   int64_t ng = 0;
   std::vector<int64_t> off;           // matrix m's entries begin at off[m]
@@ -2021,11 +2021,13 @@ static bool build_unions(Ctx* c, const std::vector<Csr>& mats, const int32_t* sc
   const int64_t pad = 6 * ng + 4;
   for (int m = 0; m < B; ++m) u.off[m + 1] = (u.off[m] + mats[m].nnz + 3 * (mats[m].nnz / kBE) + pad + 3) & ~(int64_t)3;
   const int64_t tot = u.off[B], slots = tot / kBE + (ng + 1) * B;
-  const double need = 14.0 * (double)tot + 4.0 * (double)slots + 24.0 * (double)(ng + 1) * B + extra;
+  const double need = extra + c->growth(S_CG_UCNT, 8 * (size_t)(ng + 1)) + c->growth(S_CG_UPTR, 8 * (size_t)(ng + 1) * B) +
+                      c->growth(S_CG_ULEN, 4 * (size_t)ng * B) + c->growth(S_CG_UEND, 4 * (size_t)ng * B) +
+                      c->growth(S_CG_UBATCH, 4 * (size_t)slots) + c->growth(S_CG_UCOL, 4 * (size_t)tot) +
+                      c->growth(S_CG_UVAL, 8 * (size_t)tot) + c->growth(S_CG_UPOS, 2 * (size_t)tot);
   size_t free_b = 0, total_b = 0;
-  bool fits = hipMemGetInfo(&free_b, &total_b) != hipSuccess || need <= 0.5 * (double)free_b;
-  if (c->arena) fits = fits && 1.25 * need <= (double)(c->arena_cap - c->arena_used);
-  else if (c->cap_bytes > 0) fits = fits && 1.25 * need + (double)c->held_bytes <= (double)c->cap_bytes;
+  const bool fits = (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need <= 0.5 * (double)free_b) &&
+                    1.125 * need <= c->room();
   if (!fits && c->union_spmm <= 0) return false;
   if (n >= kUnionCheckRows)
     for (const Csr& A : mats)
@@ -2157,6 +2159,13 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   double* w_red = use_pc ? c->get<double>(S_CG_WRED, (size_t)(n1 + 1) * R * B) : nullptr;
   double* p_part = use_lr ? c->get<double>(S_CG_PARTG, (size_t)n1 * R * nbu * B) : nullptr;
   double* p_red = use_lr ? c->get<double>(S_CG_GP, (size_t)n1 * R * B) : nullptr;
+  double* ha = c->get<double>(S_CG_HIST_A, (size_t)max_iter * R * B);
+  double* hb = c->get<double>(S_CG_HIST_B, (size_t)max_iter * R * B);
+  // per-member state block: doubles rz[2R], rz0[R], bnorm2[R], rr_last[R];
+  // ints act[2R], failed[R], iters[R], done, not_spd, it
+  const size_t sbytes = ((5 * (size_t)R) * 8 + (4 * (size_t)R + 3) * 4 + 255) / 256 * 256;
+  char* sb = c->get<char>(S_CG_STATE, sbytes * B);
+  SDGP_HIP(hipMemsetAsync(sb, 0, sbytes * B, c->stream));
   // Union lists of the shared-gather SpMM (automatic from kUnionMinRows rows:
   // below that, building the lists costs more than the solve saves)
   bool uni = ns > 0 && (sh.union_spmm > 0 || (sh.union_spmm < 0 && n >= kUnionMinRows));
@@ -2175,13 +2184,6 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   const int64_t nft = (n + 15) / 16;             // 16-row tiles of F
   // tile flags pay from two tiles per wavefront on (sweep_tiles)
   uint8_t* fz = fw && n > (int64_t)nbu * kBlockRows ? c->get<uint8_t>(S_CG_FTILES, (size_t)nft * B) : nullptr;
-  double* ha = c->get<double>(S_CG_HIST_A, (size_t)max_iter * R * B);
-  double* hb = c->get<double>(S_CG_HIST_B, (size_t)max_iter * R * B);
-  // per-member state block: doubles rz[2R], rz0[R], bnorm2[R], rr_last[R];
-  // ints act[2R], failed[R], iters[R], done, not_spd, it
-  const size_t sbytes = ((5 * (size_t)R) * 8 + (4 * (size_t)R + 3) * 4 + 255) / 256 * 256;
-  char* sb = c->get<char>(S_CG_STATE, sbytes * B);
-  SDGP_HIP(hipMemsetAsync(sb, 0, sbytes * B, c->stream));
   std::vector<CgArgs> hA(B);
   for (int m = 0; m < B; ++m) {
     CgArgs& A = hA[m];
@@ -2499,7 +2501,8 @@ bool taylor_terms(Ctx* c, const Csr& A, const Sorted& s, int P, int terms, uint6
   const int nbs = (int)std::min<int64_t>(round8((int64_t)kUnionPerCu * c->cu_count), round8((n + kUTile - 1) / kUTile));
   const int64_t np = (int64_t)ns * nbs;           // partials of a term
   UnionLists ul;
-  const double extra = 8.0 * (3.0 * (double)len + (double)np * terms);   // Z, V, W and the partials follow
+  const double extra = c->growth(S_CG_X, 8 * (size_t)len) + c->growth(S_CG_R, 8 * (size_t)len) +
+                       c->growth(S_CG_Q, 8 * (size_t)len) + c->growth(S_RED_OUT, 8 * (size_t)np * terms);   // (follow)
   if (!build_unions(c, {A}, s.sched, extra, ul)) return false;
   double* Z = c->get<double>(S_CG_X, (size_t)len);
   double* V = c->get<double>(S_CG_R, (size_t)len);

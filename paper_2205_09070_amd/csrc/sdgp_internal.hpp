@@ -144,6 +144,18 @@ struct Ctx {
     return gstream;
   }
 
+  // Bytes that get() would add to the workspace for a slot of `need` bytes (the
+  // slots of an earlier call serve again), and bytes that it may still add.
+  double growth(Slot s, size_t need) const {
+    const DevBuf& b = arena ? abuf[s] : buf[s];
+    if (b.bytes >= need) return 0.0;
+    return 1.125 * (double)need + 512.0 - (arena ? 0.0 : (double)b.bytes);
+  }
+  double room() const {
+    if (arena) return (double)(arena_cap - arena_used);
+    return cap_bytes > 0 ? (double)cap_bytes - (double)held_bytes : INFINITY;
+  }
+
   template <class T>
   T* get(Slot s, size_t count) {
     size_t need = count * sizeof(T);

@@ -7,6 +7,8 @@ from __future__ import annotations
 
 import sys
 
+import numpy as np
+
 from paper_2205_09070_amd import _lib
 from paper_2205_09070_amd import workloads as wl
 from tests.emu.emu_ctx import EmuContext
@@ -77,6 +79,38 @@ def case_cap(lib):
         c.set_option("workspace_cap", cap)
         assert _eval(c, s, est) is not None and _eval(c, w, est) is not None, "after a smaller call"
         c.close()
+
+
+def _store(lib, w, nnz, shape, lr=0):
+    """Stores a tuned shape (spmm_blocks, update_blocks, union_spmm, fw_mfma)
+    of the class of w's single evaluations with 1 to 32 probes."""
+    n = w.x.shape[0]
+    key = "emu-gfx950|u16|ni8|ns1|b1|n%d|r%d|lr%d|pc1" % (n.bit_length() - 1, round(2 * np.log2(nnz / n)), lr)
+    c = EmuContext(lib)
+    c.set_option("autotune", 2)
+    assert c.lib.sdgp_tune_cache_put(None, key.encode(), (_lib.I64 * 4)(*shape)) == _lib.OK
+
+
+def case_cap_lists(lib):
+    """Under a workspace_cap the union lists that a call built are taken by the
+    same call again, to the same bits."""
+    est = _lib.estimator(probes=4, seed=3, cg_rtol=1e-2, cg_max_iter=400, precond=1)
+    w = small(n=130)
+    nnz = EmuContext(lib).kernel_nnz(w.desc, w.x, w.h)
+    _store(lib, w, nnz, (8, 8, 1, 1))
+    seen = set()
+    for k in range(12):
+        c = EmuContext(lib)
+        c.set_option("autotune", 2)
+        c.set_option("workspace_cap", int(400000 * 1.08 ** k))
+        a, b = _eval(c, w, est), _eval(c, w, est)
+        print("cap %d: %s, again %s" % (c.get_option("workspace_cap"), a and a[2], b and b[2]))
+        assert c.get_option("last_tuned") == 1
+        if a is not None:
+            seen.add(a[2][2])
+            assert b is not None and a[2] == b[2] and a[0] == b[0] and (a[1] == b[1]).all()
+        c.close()
+    assert seen == {0, 1}                   # caps on both sides
 
 
 if __name__ == "__main__":

@@ -21,11 +21,12 @@ def emu_lib(tmp_path_factory):
     shutil.rmtree(lib + ".src", ignore_errors=True)
 
 
-@pytest.mark.parametrize("case", ["timing", "cap"])
-def test_path(emu_lib, case):
+@pytest.mark.parametrize("case", ["timing", "cap", "cap_lists"])
+def test_path(emu_lib, case, tmp_path):
     from tests.emu import emu_ctx
     r = subprocess.run([sys.executable, "-u", os.path.join(ROOT, "tests", "emu", "paths.py"), emu_lib, case],
-                       env=emu_ctx.emu_env(), capture_output=True, text=True, timeout=600, cwd=ROOT)
+                       env=emu_ctx.emu_env({"SDGP_TUNE_CACHE": str(tmp_path / "tune.json")}), capture_output=True,
+                       text=True, timeout=600, cwd=ROOT)
     print(r.stdout[-4000:])
     print(r.stderr[-6000:])
     assert r.returncode == 0 and "case %s holds" % case in r.stdout
