@@ -1873,6 +1873,7 @@ int64_t update_tiles(int64_t n, bool fw) {
 // on; the shapes change only the order of floating-point sums.
 constexpr int kTrialIters = 24;
 constexpr int kTrialSkip = 8;
+constexpr double kTrialRefused = -2.0;   // trial_ms of a trial whose union lists do not fit
 constexpr int64_t kTuneMinRows = 65536;
 
 struct ShapeGuard {   // leaves trial mode on every exit path
@@ -1896,7 +1897,8 @@ std::string tune_key(const Ctx* c, int NI, int ns, int B, int64_t n, int64_t nnz
 }  // namespace
 
 // Trial solves of the tuner (see above); returns the fastest shape, with
-// ms_per_iter < 0 when the solve is too short to time.
+// ms_per_iter < 0 when the solve is too short to time.  A trial whose union
+// lists do not fit is not run (it would time the CSR form under their name).
 static TuneChoice run_tuner(Ctx* c, const std::vector<CgMember>& mem, const Sorted& s, const double* ys, int kind,
                             int P, uint64_t seed, double rtol, const double* dense_rhs, int dense_R, int NI,
                             int ns, int64_t n, int n1) {
@@ -1929,6 +1931,11 @@ static TuneChoice run_tuner(Ctx* c, const std::vector<CgMember>& mem, const Sort
   best.update_blocks = (int)std::max<int64_t>(
       1, std::min<int64_t>({(int64_t)kMaxNbu, (int64_t)round1, update_tiles(n, best.fw_mfma != 0)}));
   double t_best = trial(best);
+  if (t_best == kTrialRefused) {                 // lists that do not fit: the CSR form is the default
+    best.union_spmm = 0;
+    best.spmm_blocks = spmm_grids(0)[0];
+    t_best = trial(best);
+  }
   best.default_ms_per_iter = t_best;
   best.ms_per_iter = t_best;
   if (t_best <= 0.0) return best;
@@ -2174,6 +2181,10 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     std::vector<Csr> mats(B);
     for (int m = 0; m < B; ++m) mats[m] = mem[m].A;
     uni = build_unions(c, mats, s.sched, 0.0, ul);
+    if (!uni && c->in_trial) {
+      c->trial_ms = kTrialRefused;
+      return {};
+    }
   }
   // union-list SpMM: one resident round of blocks unless a grid was chosen
   // (0.180 / 0.186 ms per launch with one / two rounds at 400,000 points)

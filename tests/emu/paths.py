@@ -5,7 +5,10 @@ child process started with emu_env():
 """
 from __future__ import annotations
 
+import os
+import re
 import sys
+import tempfile
 
 import numpy as np
 
@@ -111,6 +114,44 @@ def case_cap_lists(lib):
             assert b is not None and a[2] == b[2] and a[0] == b[0] and (a[1] == b[1]).all()
         c.close()
     assert seen == {0, 1}                   # caps on both sides
+
+
+def _traced(call):
+    """The launches of call() as (kernel, grid x, grid y, grid z)."""
+    with tempfile.TemporaryFile() as f:
+        sys.stderr.flush()
+        old = os.dup(2)
+        os.dup2(f.fileno(), 2)
+        os.environ["EMU_TRACE"] = "1"
+        try:
+            call()
+        finally:
+            del os.environ["EMU_TRACE"]
+            os.dup2(old, 2)
+            os.close(old)
+        f.seek(0)
+        text = f.read().decode()
+    return [(m[0], int(m[1]), int(m[2]), int(m[3]))
+            for m in re.findall(r"\[hipemu\] (\S.*?) grid \((\d+),(\d+),(\d+)\)", text)]
+
+
+def case_refused_trial(lib):
+    """The tuner times no candidate whose union lists the workspace_cap refuses
+    (one step of CSR rows has 16 rows, of the lists 64: at 130 points 16 blocks
+    and 8)."""
+    est = _lib.estimator(probes=4, seed=3, cg_rtol=1e-8, cg_max_iter=400, precond=1)
+    w = small(n=130)
+    forms = {}
+    for cap in (0, 470000):
+        c = EmuContext(lib)
+        c.set_option("autotune", 2)
+        c.set_option("workspace_cap", cap)
+        os.environ["SDGP_TUNE_CACHE"] += "x"
+        lines = _traced(lambda: c.lml_grad(w.desc, w.x, w.y, w.h, est))
+        forms[cap] = {ln[:2] for ln in lines if ln[0].startswith("k_cg_spmm")}
+        print("cap %d: %s" % (cap, sorted(forms[cap])))
+    assert forms[0] == {("k_cg_spmm<1>", 16), ("k_cg_spmm_u<1, false>", 8)}
+    assert forms[470000] == {("k_cg_spmm<1>", 16)}
 
 
 if __name__ == "__main__":
