@@ -43,6 +43,11 @@ constexpr int kUTile = 4 * kGR;  // rows per block step of the union-list SpMM
 constexpr int kBE = 64;          // list columns per batch of the union-list SpMM (one per lane)
 constexpr int kBS = 6;           // its logarithm
 constexpr int kUnionPerCu = 4;   // resident blocks of the union-list SpMM per CU (its launch bounds)
+// Blocks per CU of the CSR SpMM on column 0 alone: one resident round.  376
+// iterations alone with 1024 / 2048 / 8192 / 32768 blocks (60 entries per row in
+// 3-D): 33.7 / 31.1 / 32.2 / 32.2 ms at 100,000 points, 89.6 / 73.0 / 74.8 / 77.4
+// at 400,000, 193 / 151 / 153 / 157 at 1,000,000.
+constexpr int kTailPerCu = 8;
 constexpr int kSlab = 32;        // columns per slab
 constexpr int kSC = kSlab + 1;   // LDS stride of per-column values (slab columns + column 0)
 constexpr int kMaxNbs = 32768;   // SpMM blocks
@@ -1775,7 +1780,7 @@ void launch_iteration(hipStream_t st, const CgArgs* dA, const Launch& L, Ctx* c)
     SDGP_HIP(hipEventRecord(e1, st));
     c->spmm_events.push_back({e0, e1});
   }
-  k_cg_colsum<<<dim3(L.R, 1, L.B), kSumT, 0, st>>>(dA, 0);
+  k_cg_colsum<<<dim3(L.ns == 0 ? 1 : L.R, 1, L.B), kSumT, 0, st>>>(dA, 0);   // (column 0 alone: its partials only)
   SDGP_CHECK_LAUNCH();
   if (L.fz) k_cg_update_xr<NI, 2><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else if (L.fw) k_cg_update_xr<NI, 1><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
@@ -2144,8 +2149,17 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
       }
     }
   }
-  const int64_t nbs_cap = sh.spmm_blocks > 0 ? sh.spmm_blocks : kMaxNbs;
-  int nbs = (int)std::min<int64_t>(nbs_cap, round8(tiles));
+  // Union lists of the shared-gather SpMM (automatic from kUnionMinRows rows:
+  // below that, building the lists costs more than the solve saves)
+  bool uni = ns > 0 && (sh.union_spmm > 0 || (sh.union_spmm < 0 && n >= kUnionMinRows));
+  // The SpMM grid over CSR rows.  A tuned grid belongs to the form that it was
+  // tuned with: lists that do not fit leave theirs, and so does column 0 when it
+  // goes alone (see kTailPerCu).
+  const int64_t nbs_cap = sh.spmm_blocks > 0 && (user_shape || !uni) ? sh.spmm_blocks : kMaxNbs;
+  const int nbs_csr = (int)std::min<int64_t>(nbs_cap, round8(tiles));
+  const int nbs_y = user_shape && sh.spmm_blocks > 0
+                        ? nbs_csr
+                        : (int)std::min<int64_t>(round8((int64_t)kTailPerCu * c->cu_count), round8(tiles));
   // F w products of the update kernels on the matrix cores (measured faster at
   // 16 and at 32 bump functions); 0 per-row broadcasts
   const bool fw = ns > 0 && n1 > 0 && sh.fw_mfma != 0;
@@ -2173,9 +2187,6 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   const size_t sbytes = ((5 * (size_t)R) * 8 + (4 * (size_t)R + 3) * 4 + 255) / 256 * 256;
   char* sb = c->get<char>(S_CG_STATE, sbytes * B);
   SDGP_HIP(hipMemsetAsync(sb, 0, sbytes * B, c->stream));
-  // Union lists of the shared-gather SpMM (automatic from kUnionMinRows rows:
-  // below that, building the lists costs more than the solve saves)
-  bool uni = ns > 0 && (sh.union_spmm > 0 || (sh.union_spmm < 0 && n >= kUnionMinRows));
   UnionLists ul;
   if (uni) {
     std::vector<Csr> mats(B);
@@ -2188,10 +2199,12 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   }
   // union-list SpMM: one resident round of blocks unless a grid was chosen
   // (0.180 / 0.186 ms per launch with one / two rounds at 400,000 points)
-  if (uni)
-    nbs = (int)std::min<int64_t>(sh.spmm_blocks > 0 ? nbs : round8((int64_t)kUnionPerCu * c->cu_count),
-                                 round8((n + kUTile - 1) / kUTile));
-  double* s_part = c->get<double>(S_CG_PART, (size_t)R * nbs * B);
+  const int nbs = uni ? (int)std::min<int64_t>(sh.spmm_blocks > 0 ? sh.spmm_blocks : round8((int64_t)kUnionPerCu * c->cu_count),
+                                               round8((n + kUTile - 1) / kUTile))
+                      : nbs_csr;
+  // y alone (see try_tail below)
+  const bool tail_ok = B == 1 && ns > 0 && probe_cols && prt > rtol && !c->in_trial;
+  double* s_part = c->get<double>(S_CG_PART, std::max((size_t)R * nbs * B, tail_ok ? (size_t)nbs_y : 0));
   const int64_t nft = (n + 15) / 16;             // 16-row tiles of F
   // tile flags pay from two tiles per wavefront on (sweep_tiles)
   uint8_t* fz = fw && n > (int64_t)nbu * kBlockRows ? c->get<uint8_t>(S_CG_FTILES, (size_t)nft * B) : nullptr;
@@ -2301,8 +2314,8 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   // (they stop first when their tolerance is looser than y's), the rest of
   // y's solve runs the column-0 kernels only -- the CSR SpMM of column 0
   // and the column-0 blocks of the update kernels -- with the device
-  // arguments' slab count set to 0 (restored for the unpack).
-  const bool tail_ok = B == 1 && ns > 0 && probe_cols && prt > rtol && !c->in_trial;
+  // arguments' slab count set to 0 and that kernel's grid (restored for the
+  // unpack).
   bool tail = false;
   int tail_from = 0;                              // iterations executed when y went alone
   std::vector<int32_t> act_h((size_t)2 * R);
@@ -2320,10 +2333,13 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
     L.ns = 0;
     L.uni = false;
     L.fw = L.fz = false;
+    L.nbs = nbs_y;
     hA[0].ns = 0;
+    hA[0].nbs = nbs_y;
     SDGP_HIP(hipMemcpyAsync(dA, hA.data(), sizeof(CgArgs), hipMemcpyHostToDevice, st));
     SDGP_HIP(hipStreamSynchronize(st));
     hA[0].ns = ns;
+    hA[0].nbs = nbs;
     return true;
   };
   c->spmm_events.clear();

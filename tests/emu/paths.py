@@ -154,6 +154,36 @@ def case_refused_trial(lib):
     assert forms[470000] == {("k_cg_spmm<1>", 16)}
 
 
+def case_csr_grid(lib):
+    """The SpMM over CSR rows has its own grid (16 rows a step) where the union
+    lists' (64 rows a step) does not apply: when column 0 goes alone after the
+    lists, and when tuned lists do not fit."""
+    w = small(n=400)
+    c = EmuContext(lib)
+    c.set_option("union_spmm", 1)
+    est = _lib.estimator(probes=1, seed=3, cg_rtol=1e-9, probe_rtol=1e-1, cg_max_iter=400, precond=1)
+    lines = _traced(lambda: c.lml_grad(w.desc, w.x, w.y, w.h, est))
+    grids = {ln[:2] for ln in lines if ln[0].startswith("k_cg_spmm")}
+    print("alone for %d iterations: %s" % (c.get_option("last_y_tail"), sorted(grids)))
+    assert c.get_option("last_y_tail") > 0
+    assert grids == {("k_cg_spmm_u<1, false>", 8), ("k_cg_spmm<0>", 32)}
+    v, g, _ = c.lml_grad(w.desc, w.x, w.y, w.h, est)
+    c.set_option("union_spmm", 0)
+    v0, g0, _ = c.lml_grad(w.desc, w.x, w.y, w.h, est)
+    assert abs(v - v0) <= 1e-9 * abs(v0) and np.abs(g - g0).max() <= 1e-7 * np.abs(g0).max()
+
+    w = small(n=130)
+    _store(lib, w, EmuContext(lib).kernel_nnz(w.desc, w.x, w.h), (8, 8, 1, 1))
+    est = _lib.estimator(probes=4, seed=3, cg_rtol=1e-2, cg_max_iter=400, precond=1)
+    for cap, shape in ((0, [8, 8, 1]), (470000, [16, 8, 0])):
+        c = EmuContext(lib)
+        c.set_option("autotune", 2)
+        c.set_option("workspace_cap", cap)
+        got = _eval(c, w, est)[2]
+        print("cap %d: %s" % (cap, got))
+        assert got == shape and c.get_option("last_tuned") == 1
+
+
 if __name__ == "__main__":
     globals()["case_" + sys.argv[2]](sys.argv[1])
     print("case %s holds" % sys.argv[2], flush=True)
