@@ -58,7 +58,7 @@ struct ColArgs {
   const double* dense;
   double *X, *V;            // [n][R] (V: M^{-1} b, may be null)
   double* xw;               // [R][npad] x by place
-  double *hist_a, *hist_b;  // [max_iter][R]
+  double *hist_a, *hist_b;  // [max_iter][R] (null: not kept)
   double *rz0, *bn, *rl;    // [R]
   int32_t *iters, *flags;   // [R] (flags: 1 failed, 2 still iterating at max_iter)
   int none;                 // 0 (see slice_of in k_col_cg)
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(64 * W) void k_col_cg(const ColArgs* __restrict__ A
           failed[q] = true;
           act[q] = false;
         }
-        if (threadIdx.x == 0) ((GL double*)A.hist_a)[(int64_t)it * R + rc0 + q] = alpha[q];
+        if (threadIdx.x == 0 && A.hist_a) ((GL double*)A.hist_a)[(int64_t)it * R + rc0 + q] = alpha[q];
       }
       rr[q] = 0.0;
     }
@@ -542,7 +542,7 @@ __global__ __launch_bounds__(64 * W) void k_col_cg(const ColArgs* __restrict__ A
         rl[q] = rr[q];
         ++its[q];
         act[q] = !(rr[q] <= (rc0 + q == 0 ? A.rtol2 : A.prtol2) * bb[q]);
-        if (threadIdx.x == 0) ((GL double*)A.hist_b)[(int64_t)it * R + rc0 + q] = beta[q];
+        if (threadIdx.x == 0 && A.hist_a) ((GL double*)A.hist_b)[(int64_t)it * R + rc0 + q] = beta[q];
       }
     }
     // p = M^{-1} r + beta p
@@ -678,8 +678,10 @@ std::vector<CgResult> column_cg(Ctx* c, const std::vector<CgMember>& mem, const 
   dv2* val = c->get<dv2>(S_COL_VAL, (size_t)soff[B] * 128);
   uv2* col = c->get<uv2>(S_COL_COL, (size_t)soff[B] * 64);
   double* FT = n1 > 0 ? c->get<double>(S_COL_FT, (size_t)n1 * npad * B) : nullptr;
-  double* ha = c->get<double>(S_CG_HIST_A, (size_t)max_iter * R * B);
-  double* hb = c->get<double>(S_CG_HIST_B, (size_t)max_iter * R * B);
+  // the coefficients are read by the quadrature of probe columns only
+  const bool keep_hist = kind == PK_RADEMACHER || kind == PK_IDENTITY;
+  double* ha = keep_hist ? c->get<double>(S_CG_HIST_A, (size_t)max_iter * R * B) : nullptr;
+  double* hb = keep_hist ? c->get<double>(S_CG_HIST_B, (size_t)max_iter * R * B) : nullptr;
   double* sd = c->get<double>(S_COL_STATE, (size_t)R * B * 3);          // rz0, bn, rl of every member
   int32_t* si = c->get<int32_t>(S_CG_STATE, (size_t)R * B * 2);         // iters, flags
   std::vector<ColArgs> hA(B);
@@ -705,8 +707,8 @@ std::vector<CgResult> column_cg(Ctx* c, const std::vector<CgMember>& mem, const 
     A.X = X + m * NR;
     A.V = V ? V + m * NR : nullptr;
     A.xw = xw + (size_t)m * npad * R;
-    A.hist_a = ha + (size_t)m * max_iter * R;
-    A.hist_b = hb + (size_t)m * max_iter * R;
+    A.hist_a = keep_hist ? ha + (size_t)m * max_iter * R : nullptr;
+    A.hist_b = keep_hist ? hb + (size_t)m * max_iter * R : nullptr;
     A.rz0 = sd + (size_t)m * R * 3;
     A.bn = A.rz0 + R;
     A.rl = A.bn + R;

@@ -319,7 +319,7 @@ struct CgResult {
   bool not_spd;
   bool converged;
   double* X;        // [n, R] solution block (device, context-owned)
-  double* hist_a;   // [max_iter, R] CG alphas
+  double* hist_a;   // [max_iter, R] CG alphas (column CG without probe columns: null)
   double* hist_b;   // [max_iter, R] CG betas
   int32_t* col_iters;  // [R] device iterations per column
   int R;

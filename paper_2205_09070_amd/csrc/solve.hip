@@ -317,10 +317,19 @@ void posterior_solve(Ctx* c, const Csr& A, const Sorted& s, const double* ys, co
   const char* bad = "CG met p^T A p <= 0: the covariance is not positive definite";
   *converged = true;
   // Column CG: y is column 0 of the first chunk, and a chunk fills the GPU's
-  // CUs with columns (chunks of 64 leave most of them idle)
+  // CUs with columns (chunks of 64 leave most of them idle).  Its right-hand
+  // sides, solutions and working copies of them (three blocks of 1024 columns at
+  // most) are taken only from memory that is free twice over; otherwise the
+  // narrow chunks, which need a sixteenth.
   const int wide = (int)std::min<int64_t>(1023, n0);
   const int n1 = pc ? pc->n1 : 0;
-  const bool cols = column_cg_chosen(c) && column_cg_applies(c, n, A.nnz, 1 + wide, 1, n1, true, max_iter);
+  bool cols = column_cg_chosen(c) && column_cg_applies(c, n, A.nnz, 1 + wide, 1, n1, false, max_iter);
+  if (cols) {
+    const size_t block = sizeof(double) * (size_t)(n + 63) * (1 + wide);
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess)
+      cols = c->growth(S_POST, block) + c->growth(S_CG_P, block) + c->growth(S_CG_X, block) <= 0.5 * (double)free_b;
+  }
   const int step = cols ? wide : kWave;
   if (!cols) {
     CgResult cg = block_cg(c, A, s, ys, PK_NONE, 0, 0, rtol, max_iter, nullptr, 0, pc, false, nullptr);
@@ -341,7 +350,9 @@ void posterior_solve(Ctx* c, const Csr& A, const Sorted& s, const double* ys, co
     const unsigned g = (unsigned)((Rt + 3) / 4);
     k_scatter_chunk<<<g, 256, 0, c->stream>>>(K0.row_ptr, K0.col, K0.val, t0, Rt, n0, Rc, B + y0);
     SDGP_CHECK_LAUNCH();
-    CgResult cg = block_cg(c, A, s, nullptr, PK_DENSE, 0, 0, rtol, max_iter, B, Rc, pc, false, nullptr);
+    // (every chunk by the solver that was chosen, the last and narrower one too)
+    CgResult cg = cols ? column_cg(c, {CgMember{A, pc}}, s, nullptr, PK_DENSE, Rc, 0, rtol, rtol, max_iter, B, false)[0]
+                       : block_cg(c, A, s, nullptr, PK_DENSE, 0, 0, rtol, max_iter, B, Rc, pc, false, nullptr);
     if (cg.not_spd) throw Error(SDGP_ERR_NOT_SPD, bad);
     if (!cg.converged) *converged = false;
     if (y0) {

@@ -1,4 +1,5 @@
 """Solves near the limits of the workspace they are given."""
+import numpy as np
 import pytest
 
 from paper_2205_09070_amd import workloads as wl
@@ -40,3 +41,21 @@ def test_static_workspace_fits_whatever_the_block_cg_fits():
     assert call(1000)[1] and 1000 < column
     for m in (column, min(column + 1, fits), (column + fits) // 2, fits):
         assert call(m)[0] is not None, m
+
+
+def test_posterior_keeps_no_coefficients():
+    """cg_max_iter bounds the iterations, not the memory, of a posterior whose
+    1024 columns are solved together: at 20,000,000 (328 GB if every iteration's
+    coefficients had a place) the call gives the bits that it gives at 4000, and
+    its last, narrow chunk takes the same solver."""
+    gu.need_gpu()
+    import paper_2205_09070_amd as sd
+    w = wl.random_small(900, 2, 2, 2, 3, per_row=12.0, noise_var=1e-2)
+    x, y, x0 = gu.dev(w.x), gu.dev(w.y), gu.dev(np.random.default_rng(4).random((1030, 2)))
+    out = []
+    for max_iter in (4000, 20_000_000):
+        c = gu.ctx()
+        m, v = c.posterior_mean_var(w.desc, x, y, w.h, x0, sd.estimator(probes=1, cg_rtol=1e-12, cg_max_iter=max_iter))
+        assert c.get_option("last_spmm_blocks") == 7 and c.get_option("last_update_blocks") == 0
+        out.append((m.cpu().numpy(), v.cpu().numpy()))
+    assert (out[0][0] == out[1][0]).all() and (out[0][1] == out[1][1]).all()
