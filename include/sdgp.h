@@ -318,10 +318,11 @@ sdgp_status sdgp_lml_grad_noalloc(sdgp_ctx* ctx, const sdgp_kernel_desc* desc, c
  * factored operator (operator_form = SDGP_OPERATOR_FACTORED) is rejected
  * with INVALID_ARG before any device work.  The points
  * are ordered once (cell side = the largest core radius), every member is
- * assembled into storage of its own, and all members' block CGs advance
+ * assembled into storage of its own, and all members' CGs advance
  * together -- every solver kernel is one launch with the member as grid
- * z, so members with uneven entry counts share the GPU -- followed by each
- * member's quadrature and adjoint.  Probes are common to all members.
+ * z, so members with uneven entry counts share the GPU (block CG and, for
+ * members whose own size takes it, column CG one after the other) --
+ * followed by each member's quadrature and adjoint.  Probes are common to all members.
  * H is a host array B*n_h (member m at H[m*n_h]); lml_out: host double[B];
  * grad_out: host double[B*n_h]; member_status: host int32[B] (per-member
  * sdgp_status; one failing member does not affect the others); info: host

@@ -2112,12 +2112,32 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   const int64_t tiles = (n + kTile - 1) / kTile;
   const bool user_shape = c->spmm_blocks > 0 || c->update_blocks > 0 || c->union_spmm >= 0 || c->fw_mfma >= 0;
   // Small point sets: one workgroup per few columns (colcg.hip), unless the
-  // caller asks for a launch shape of the block CG or for tuning it
+  // caller asks for a launch shape of the block CG or for tuning it.  Each member
+  // by its own entries, as in a call of its own, so that a member's bits do not
+  // hang on the others'.
   if (column_cg_chosen(c)) {
-    int64_t nnz = 0;
-    for (const auto& mm : mem) nnz = std::max<int64_t>(nnz, mm.A.nnz);
-    if (column_cg_applies(c, n, nnz, R, B, n1, use_pc && keep_v, max_iter))
-      return column_cg(c, mem, s, ys, kind, R, seed, rtol, prt, max_iter, dense_rhs, keep_v);
+    std::vector<CgMember> part[2];                // block CG, column CG
+    std::vector<int> where(B);
+    for (int m = 0; m < B; ++m) {
+      where[m] = column_cg_applies(c, n, mem[m].A.nnz, R, n1, use_pc && keep_v, max_iter) ? 1 : 0;
+      part[where[m]].push_back(mem[m]);
+    }
+    if (part[0].empty()) return column_cg(c, mem, s, ys, kind, R, seed, rtol, prt, max_iter, dense_rhs, keep_v);
+    if (!part[1].empty()) {
+      const std::vector<CgResult> b = block_cg_multi(c, part[0], s, ys, kind, P, seed, rtol, max_iter, dense_rhs,
+                                                     dense_R, keep_v, use_graph, probe_rtol);
+      const TuneChoice shape = c->last_shape;
+      const int tuned = c->last_tuned, alone = c->last_y_tail;
+      const std::vector<CgResult> q = column_cg(c, part[1], s, ys, kind, R, seed, rtol, prt, max_iter, dense_rhs,
+                                                keep_v, true);
+      c->last_shape = shape;
+      c->last_tuned = tuned;
+      c->last_y_tail = alone;
+      std::vector<CgResult> out;
+      size_t at[2] = {0, 0};
+      for (int m = 0; m < B; ++m) out.push_back((where[m] ? q : b)[at[where[m]]++]);
+      return out;
+    }
   }
   // Launch shape: a tuner trial's candidate; else the context options when
   // any is set; else the tuned shape of this problem class (tuned now when

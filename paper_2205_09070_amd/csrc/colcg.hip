@@ -630,8 +630,9 @@ int64_t max_steps(int64_t n, int64_t nnz) { return nnz / 256 + 2 * ((n + 63) / 6
 // entries per row, 33 columns: 9.4 against 36 us; its 2,001 columns for the
 // exact likelihood: 28 against 213 us; 10,000 points, 88 entries per row, 501
 // columns: 137 us against eight solves of about 90 us.)  A population's members
-// are taken as single solves here, so that both give the same values.
-bool column_cg_applies(const Ctx* c, int64_t n, int64_t nnz, int R, int B, int n1, bool keep_v, int max_iter) {
+// are taken as single solves here, so that both give the same values; that the
+// block CG shares its launches among members does not enter.
+bool column_cg_applies(const Ctx* c, int64_t n, int64_t nnz, int R, int n1, bool keep_v, int max_iter) {
   if (n > kColMaxN || nnz < 0) return false;
   const int NC = columns_per_group(n, R, n1 > 0);
   const int64_t groups = (R + NC - 1) / NC, cu = std::max(1, c->cu_count), ns = (R - 1 + 31) / 32;
@@ -652,12 +653,12 @@ bool column_cg_applies(const Ctx* c, int64_t n, int64_t nnz, int R, int B, int n
   const double need = 8.0 * R * ((keep_v ? 2.0 : 1.0) * n + npad) + 2560.0 * max_steps(n, nnz) + 8.0 * n1 * npad +
                       hist + 9.0 * npad + 32.0 * R + 4096.0;
   const double block_need = 8.0 * (keep_v ? 5.0 : 4.0) * (n + 32.0 * ns * n) + hist;
-  return 2.25 * need * B <= (double)(c->arena_cap - c->arena_used) || need <= block_need;
+  return 2.25 * need <= (double)(c->arena_cap - c->arena_used) || need <= block_need;
 }
 
 std::vector<CgResult> column_cg(Ctx* c, const std::vector<CgMember>& mem, const Sorted& s, const double* ys, int kind,
                                 int R, uint64_t seed, double rtol, double prtol, int max_iter,
-                                const double* dense_rhs, bool keep_v) {
+                                const double* dense_rhs, bool keep_v, bool beside) {
   const int B = (int)mem.size();
   const int64_t n = s.n;
   const int S = (int)((n + 63) / 64), npad = 64 * S;
@@ -670,8 +671,10 @@ std::vector<CgResult> column_cg(Ctx* c, const std::vector<CgMember>& mem, const 
   std::vector<int64_t> soff(B + 1, 0);
   for (int m = 0; m < B; ++m) soff[m + 1] = soff[m] + max_steps(n, mem[m].A.nnz);
   const size_t NR = (size_t)n * R;
-  double* X = c->get<double>(S_CG_P, NR * B);
-  double* V = (use_pc && keep_v) ? c->get<double>(S_CG_Q, NR * B) : nullptr;
+  // (the block CG's results lie in P, Q, the state and the histories; its X, R
+  // and V are working storage)
+  double* X = c->get<double>(beside ? S_CG_R : S_CG_P, NR * B);
+  double* V = (use_pc && keep_v) ? c->get<double>(beside ? S_CG_V : S_CG_Q, NR * B) : nullptr;
   double* xw = c->get<double>(S_CG_X, (size_t)npad * R * B);
   int32_t* idx = c->get<int32_t>(S_COL_IDX, (size_t)(2 * npad + S) * B);
   int64_t* off = c->get<int64_t>(S_COL_OFF, (size_t)S * B);
@@ -680,10 +683,10 @@ std::vector<CgResult> column_cg(Ctx* c, const std::vector<CgMember>& mem, const 
   double* FT = n1 > 0 ? c->get<double>(S_COL_FT, (size_t)n1 * npad * B) : nullptr;
   // the coefficients are read by the quadrature of probe columns only
   const bool keep_hist = kind == PK_RADEMACHER || kind == PK_IDENTITY;
-  double* ha = keep_hist ? c->get<double>(S_CG_HIST_A, (size_t)max_iter * R * B) : nullptr;
-  double* hb = keep_hist ? c->get<double>(S_CG_HIST_B, (size_t)max_iter * R * B) : nullptr;
+  double* ha = keep_hist ? c->get<double>(beside ? S_COL_HIST_A : S_CG_HIST_A, (size_t)max_iter * R * B) : nullptr;
+  double* hb = keep_hist ? c->get<double>(beside ? S_COL_HIST_B : S_CG_HIST_B, (size_t)max_iter * R * B) : nullptr;
   double* sd = c->get<double>(S_COL_STATE, (size_t)R * B * 3);          // rz0, bn, rl of every member
-  int32_t* si = c->get<int32_t>(S_CG_STATE, (size_t)R * B * 2);         // iters, flags
+  int32_t* si = c->get<int32_t>(S_COL_ITERS, (size_t)R * B * 2);        // iters, flags
   std::vector<ColArgs> hA(B);
   for (int m = 0; m < B; ++m) {
     ColArgs& A = hA[m];

@@ -101,7 +101,7 @@ enum Slot {
   S_POP_IVCNT, S_POP_IVPTR, S_POP_IV, S_POP_ROWNNZ, S_POP_SCAN, S_POP_ROWPTR, S_POP_COL, S_POP_VAL, S_POP_CAND,
   S_POP_GRAM, S_POP_SINV,
   // column CG (small point sets)
-  S_COL_IDX, S_COL_OFF, S_COL_VAL, S_COL_COL, S_COL_FT, S_COL_STATE, S_CG_FTILES,
+  S_COL_IDX, S_COL_OFF, S_COL_VAL, S_COL_COL, S_COL_FT, S_COL_STATE, S_COL_ITERS, S_COL_HIST_A, S_COL_HIST_B, S_CG_FTILES,
   S_NUM
 };
 
@@ -353,10 +353,11 @@ inline bool column_cg_chosen(const Ctx* c) {
   return !c->in_trial && c->autotune != 2 && c->spmm_blocks <= 0 && c->update_blocks <= 0 && c->union_spmm < 0 &&
          c->fw_mfma < 0;
 }
-bool column_cg_applies(const Ctx* c, int64_t n, int64_t nnz, int R, int B, int n1, bool keep_v, int max_iter);
+bool column_cg_applies(const Ctx* c, int64_t n, int64_t nnz, int R, int n1, bool keep_v, int max_iter);
+// beside: the results of a block CG solve of other members stay valid.
 std::vector<CgResult> column_cg(Ctx* c, const std::vector<CgMember>& mem, const Sorted& s, const double* ys, int kind,
                                 int R, uint64_t seed, double rtol, double prtol, int max_iter,
-                                const double* dense_rhs, bool keep_v);
+                                const double* dense_rhs, bool keep_v, bool beside = false);
 Precond lowrank_precond(Ctx* c, const Sorted& s, const KParams& kp, const Bumps& b);
 // The same for every member of a population (one Gram launch, grid z =
 // member); the members' bump values are contiguous from F0 with stride

@@ -323,7 +323,7 @@ void posterior_solve(Ctx* c, const Csr& A, const Sorted& s, const double* ys, co
   // narrow chunks, which need a sixteenth.
   const int wide = (int)std::min<int64_t>(1023, n0);
   const int n1 = pc ? pc->n1 : 0;
-  bool cols = column_cg_chosen(c) && column_cg_applies(c, n, A.nnz, 1 + wide, 1, n1, false, max_iter);
+  bool cols = column_cg_chosen(c) && column_cg_applies(c, n, A.nnz, 1 + wide, n1, false, max_iter);
   if (cols) {
     const size_t block = sizeof(double) * (size_t)(n + 63) * (1 + wide);
     size_t free_b = 0, total_b = 0;

@@ -184,6 +184,35 @@ def case_csr_grid(lib):
         assert got == shape and c.get_option("last_tuned") == 1
 
 
+def sides(n=820, noise=4.0):
+    """A population whose members lie on both sides of the column CG's rule (the
+    first: every pair stored) and the same with an invalid first member."""
+    w = small(n=n, n1=2)
+    p = wl.unpack_hyper(w.desc, w.h)
+    one = lambda s2, rc: wl.pack_hyper(w.desc, s2, rc, p["a"], p["beta"], p["r"], p["c"], noise)
+    H = np.array([one(0.7, 2.0), one(1.0, p["r_core"]), one(0.5, 2.0), one(1.2, 0.8 * p["r_core"])])
+    bad = H.copy()
+    bad[0, 0] = bad[2, 0] = -1.0
+    return w, H, bad
+
+
+def case_sides(lib):
+    """Members take the solver that their own entries call for: what the others
+    store does not change their bits."""
+    w, H, bad = sides()
+    est = _lib.estimator(probes=2, seed=3, cg_rtol=1e-3, cg_max_iter=200, precond=1)
+    c = EmuContext(lib)
+    v, g, st, info = c.lml_grad_batched(w.desc, w.x, w.y, H, est)
+    print("entries %s, blocks %d" % ([i.nnz for i in info], c.get_option("last_update_blocks")))
+    assert (st == 0).all() and c.get_option("last_update_blocks") > 0
+    v1, g1, st1, _ = c.lml_grad_batched(w.desc, w.x, w.y, bad, est)
+    assert list(st1) == [_lib.INVALID_ARG, 0, _lib.INVALID_ARG, 0] and c.get_option("last_update_blocks") == 0
+    assert (v[1::2] == v1[1::2]).all() and (g[1::2] == g1[1::2]).all()
+    for m in (0, 2):                        # the largest core radius: the single call's order
+        v1, g1, _ = c.lml_grad(w.desc, w.x, w.y, H[m], est)
+        assert v[m] == v1 and (g[m] == g1).all()
+
+
 if __name__ == "__main__":
     globals()["case_" + sys.argv[2]](sys.argv[1])
     print("case %s holds" % sys.argv[2], flush=True)
