@@ -92,7 +92,7 @@ struct Assembled {
 };
 
 Assembled assemble_all(Ctx* c, const Sorted& s, const sdgp_kernel_desc& d, const double* h, bool add_noise,
-                       PhaseTimer* t, bool core_only = false, const CsrOut* out = nullptr) {
+                       PhaseTimer* t, bool core_only = false, const CsrOut* out = nullptr, CanonRows* canon = nullptr) {
   Assembled r;
   r.kp = make_params(d, h);
   r.b = bump_precompute(c, s, r.kp, h);
@@ -101,7 +101,7 @@ Assembled assemble_all(Ctx* c, const Sorted& s, const sdgp_kernel_desc& d, const
   int2* iv;
   prune(c, s, r.kp, r.b, &iv_ptr, &iv, core_only);
   if (t) t->mark(3);
-  r.A = assemble_sorted(c, s, r.kp, r.b, iv_ptr, iv, add_noise, &r.candidates, t, core_only, out);
+  r.A = assemble_sorted(c, s, r.kp, r.b, iv_ptr, iv, add_noise, &r.candidates, t, core_only, out, canon);
   if (t) t->mark(5);
   return r;
 }
@@ -271,11 +271,12 @@ sdgp_status sdgp_kernel_assemble(sdgp_ctx* ctx, const sdgp_kernel_desc* desc, co
     require(desc && x && nnz_out && row_ptr, "NULL argument");
     validate(*desc, h, n);
     Sorted s = order_points(ctx, x, n, desc->dim, h[1], false);
-    Assembled as = assemble_all(ctx, s, *desc, h, add_noise != 0, nullptr);
+    CanonRows canon;
+    Assembled as = assemble_all(ctx, s, *desc, h, add_noise != 0, nullptr, false, nullptr, &canon);
     *nnz_out = as.A.nnz;
     if (as.A.nnz > capacity) throw Error(SDGP_ERR_CAPACITY, "capacity smaller than nnz");
     require(col && val, "NULL col/val");
-    canonicalize(ctx, s, as.A, row_ptr, col, val);
+    canonicalize(ctx, s, as.A, canon, row_ptr, col, val);
     SDGP_HIP(hipStreamSynchronize(ctx->stream));
   });
   return st;

@@ -1246,32 +1246,54 @@ __global__ void k_pack_points(const double* __restrict__ x, int64_t n, int dim, 
 
 // ---------------------------------------------------------- canonical CSR
 constexpr int kCanonRow = 512;    // longest row of the rank sort
+// Row lengths in caller order, and the rows past kCanonRow (sorted positions, in
+// any order; tot[1] counts them, zeroed beforehand, an atomic per wavefront that
+// meets one); tot[2]: the entry count, to be read back in the same copy.
 __global__ void k_canon_len(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ perm,
-                            int64_t n, int64_t* __restrict__ len, int* __restrict__ longest) {
+                            int64_t n, int64_t* __restrict__ len, int32_t* __restrict__ rows,
+                            unsigned long long* __restrict__ tot) {
   int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t m = s < n ? row_ptr[s + 1] - row_ptr[s] : 0;
   if (s < n) len[perm[s]] = m;
-  if (s == 0) len[n] = 0;
-  if (m > kCanonRow) atomicMax(longest, (int)m);
+  if (s == 0) {
+    len[n] = 0;
+    tot[2] = (unsigned long long)row_ptr[n];
+  }
+  const bool over = m > kCanonRow;
+  const uint64_t b = ballot64(over);
+  if (b == 0) return;                               // uniform over the wavefront
+  unsigned long long at = 0;
+  const int first = __builtin_ctzll(b);
+  if (lane_id() == first) at = atomicAdd(tot + 1, (unsigned long long)__popcll(b));
+  at = readlane_u64(at, first);
+  if (over) rows[at + lanes_below(b)] = (int32_t)s;
 }
 
+// Row rows[r] (null: every row, r < nr) in caller columns to its place of the
+// output, for the segmented sort of the places seg[r] .. seg[nr + r].  One
+// wavefront per row.
 __global__ void k_canon_copy(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                              const double* __restrict__ val, const int32_t* __restrict__ perm,
-                             int64_t n, const int64_t* __restrict__ out_ptr,
-                             int32_t* __restrict__ col2, double* __restrict__ val2) {
-  const int64_t s = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  if (s >= n) return;
+                             const int32_t* __restrict__ rows, int64_t nr, const int64_t* __restrict__ out_ptr,
+                             int64_t* __restrict__ seg, int32_t* __restrict__ col2, double* __restrict__ val2) {
+  const int64_t r = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+  if (r >= nr) return;
   const int lane = lane_id();
-  const int64_t src = row_ptr[s], len = row_ptr[s + 1] - src;
+  const int64_t s = rows ? (int64_t)rows[r] : r, src = row_ptr[s], len = row_ptr[s + 1] - src;
   const int64_t dst = out_ptr[perm[s]];
+  if (rows && lane == 0) {
+    seg[r] = dst;
+    seg[nr + r] = dst + len;
+  }
   for (int64_t k = lane; k < len; k += kWave) {
     col2[dst + k] = perm[col[src + k]];
     val2[dst + k] = val[src + k];
   }
 }
 
-// All rows straight to their sorted place when none is longer than kCanonRow:
-// one wavefront per row keeps the caller columns in LDS and gives each its rank
+// Rows of up to kCanonRow entries straight to their sorted place (the longer
+// ones go through k_canon_copy and a segmented sort, see canonicalize): one
+// wavefront per row keeps the caller columns in LDS and gives each its rank
 // among them (a row's columns differ).  Bound by the m^2 comparisons of a row of
 // m entries instead of a copy and a segmented radix sort's passes.  100,000
 // points, kernel_assemble per call: 32 entries per row 0.65 -> 0.53 ms, 96 0.73
@@ -1616,14 +1638,14 @@ __global__ void k_cell_cands_pop(const int32_t* __restrict__ cell_start, int64_t
 // Count (recording keep masks), device-wide scan, host read of nnz, fill
 // from the masks.
 static Csr assemble_two_pass(Ctx* c, const Sorted& s, RowArgs A, int64_t* candidates, PhaseTimer* t,
-                             const CsrOut* out) {
+                             const CsrOut* out, CanonRows* canon) {
   const int64_t n = s.n;
   const int64_t ncell = s.grid.n_cells;
   // keep masks of the count for the fill: offsets per cell, then storage;
   // the candidate pairs on the way
   int64_t* mwords = c->get<int64_t>(S_MASK_CNT, ncell + 1);
   unsigned long long* cand = c->get<unsigned long long>(S_COUNTER, 4);
-  SDGP_HIP(hipMemsetAsync(cand, 0, sizeof(unsigned long long), c->stream));
+  SDGP_HIP(hipMemsetAsync(cand, 0, 2 * sizeof(unsigned long long), c->stream));   // + the long rows' count
   k_mask_words<<<grid_for(ncell + 1, kBlock), kBlock, 0, c->stream>>>(s.cell_start, A.iv_ptr, A.iv, ncell, mwords,
                                                                       cand);
   SDGP_CHECK_LAUNCH();
@@ -1646,12 +1668,22 @@ static Csr assemble_two_pass(Ctx* c, const Sorted& s, RowArgs A, int64_t* candid
   SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, row_nnz, row_ptr, (int)(n + 1), c->stream));
   void* tmp = c->get<char>(S_SORT_TMP, tb);
   SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, row_nnz, row_ptr, (int)(n + 1), c->stream));
-  int64_t nnz = 0;
-  unsigned long long ncand = 0;
-  SDGP_HIP(hipMemcpyAsync(&nnz, row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
-  SDGP_HIP(hipMemcpyAsync(&ncand, cand, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
+  // read back: candidates and entries, for the canonical order also the long rows
+  unsigned long long tot[3] = {0, 0, 0};
+  if (canon) {
+    canon->len = c->get<int64_t>(S_ROWLEN2, n + 1);
+    canon->rows = c->get<int32_t>(S_CANON_ROWS, n);
+    k_canon_len<<<grid_for(n, kBlock), kBlock, 0, c->stream>>>(row_ptr, s.perm, n, canon->len, canon->rows, cand);
+    SDGP_CHECK_LAUNCH();
+    SDGP_HIP(hipMemcpyAsync(tot, cand, sizeof(tot), hipMemcpyDeviceToHost, c->stream));
+  } else {
+    SDGP_HIP(hipMemcpyAsync(tot, cand, sizeof(tot[0]), hipMemcpyDeviceToHost, c->stream));
+    SDGP_HIP(hipMemcpyAsync(tot + 2, row_ptr + n, sizeof(tot[2]), hipMemcpyDeviceToHost, c->stream));
+  }
   SDGP_HIP(hipStreamSynchronize(c->stream));
-  if (candidates) *candidates = (int64_t)ncand;
+  const int64_t nnz = (int64_t)tot[2];
+  if (canon) canon->n_long = (int64_t)tot[1];
+  if (candidates) *candidates = (int64_t)tot[0];
   if (t) t->mark(4);
   Csr k;
   if (out && nnz > out->capacity) {   // the caller's arrays are too small: no fill
@@ -1668,10 +1700,10 @@ static Csr assemble_two_pass(Ctx* c, const Sorted& s, RowArgs A, int64_t* candid
 
 Csr assemble_sorted(Ctx* c, const Sorted& s, const KParams& kp, const Bumps& b, const int32_t* iv_ptr,
                     const int2* iv, bool add_noise, int64_t* candidates, PhaseTimer* t, bool core_only,
-                    const CsrOut* out) {
+                    const CsrOut* out, CanonRows* canon) {
   require(s.grid.n_cells < 0x7fffffff, "too many cells");
   RowArgs A = row_args(s, kp, b, iv_ptr, iv, add_noise, core_only);
-  return assemble_two_pass(c, s, A, candidates, t, out);
+  return assemble_two_pass(c, s, A, candidates, t, out, canon);
 }
 
 std::vector<PopAssembled> assemble_population(Ctx* c, const Sorted& s, const sdgp_kernel_desc& d,
@@ -1927,40 +1959,43 @@ Csr assemble_cross(Ctx* c, const Sorted& s, const KParams& kp, const Bumps& b, c
   return k;
 }
 
-void canonicalize(Ctx* c, const Sorted& s, const Csr& k, int64_t* row_ptr, int32_t* col, double* val) {
+void canonicalize(Ctx* c, const Sorted& s, const Csr& k, const CanonRows& cr, int64_t* row_ptr, int32_t* col,
+                  double* val) {
+  // Long rows past a quarter take the short ones along through the sort: a row of
+  // 512 is a chain of 43 us in the rank kernel, however few there are, and the
+  // sort's own kernel for short rows took 21 us at 13,000 of them (20,000 rows, a
+  // third of them long: 0.98 ms together, 1.01 apart; 100,000 rows, 3% long: 0.79
+  // together, 0.66 apart).
   const int64_t n = s.n;
+  const bool all = 4 * cr.n_long > n;
+  const int64_t nr = all ? n : cr.n_long;
   require(k.nnz < (int64_t)0x7fffffff, "canonical CSR output needs nnz < 2^31");
-  int64_t* len = c->get<int64_t>(S_ROWLEN2, n + 2);   // + the longest row past kCanonRow
-  int* longest = reinterpret_cast<int*>(len + n + 1);
-  SDGP_HIP(hipMemsetAsync(longest, 0, sizeof(int64_t), c->stream));
-  k_canon_len<<<grid_for(n, kBlock), kBlock, 0, c->stream>>>(k.row_ptr, s.perm, n, len, longest);
-  SDGP_CHECK_LAUNCH();
   size_t tb = 0;
-  SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, len, row_ptr, (int)(n + 1), c->stream));
+  SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cr.len, row_ptr, (int)(n + 1), c->stream));
   void* tmp = c->get<char>(S_SORT_TMP, tb);
-  SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, len, row_ptr, (int)(n + 1), c->stream));
-  int most = 0;
-  SDGP_HIP(hipMemcpyAsync(&most, longest, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-  SDGP_HIP(hipStreamSynchronize(c->stream));
-  if (most == 0) {
+  SDGP_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cr.len, row_ptr, (int)(n + 1), c->stream));
+  if (nr < n) {
     k_canon_rank<<<grid_for(n, kBlock / kWave), kBlock, 0, c->stream>>>(k.row_ptr, k.col, k.val, s.perm, n, row_ptr, col,
                                                                         val);
     SDGP_CHECK_LAUNCH();
-    return;
   }
+  if (nr == 0) return;
+  int64_t* seg = all ? nullptr : c->get<int64_t>(S_CANON_SEG, 2 * nr);
   int32_t* col2 = c->get<int32_t>(S_COL2, k.nnz);
   double* val2 = c->get<double>(S_VAL2, k.nnz);
-  k_canon_copy<<<grid_for(n, kBlock / kWave), kBlock, 0, c->stream>>>(k.row_ptr, k.col, k.val, s.perm, n,
-                                                                       row_ptr, col2, val2);
+  k_canon_copy<<<grid_for(nr, kBlock / kWave), kBlock, 0, c->stream>>>(k.row_ptr, k.col, k.val, s.perm,
+                                                                        all ? nullptr : cr.rows, nr, row_ptr, seg, col2,
+                                                                        val2);
   SDGP_CHECK_LAUNCH();
+  const int64_t *begin = all ? row_ptr : seg, *end = all ? row_ptr + 1 : seg + nr;
   int bits = 1;
   while (((int64_t)1 << bits) < n) ++bits;
   tb = 0;
-  SDGP_HIP(hipcub::DeviceSegmentedRadixSort::SortPairs(nullptr, tb, col2, col, val2, val, (int)k.nnz, (int)n,
-                                                       row_ptr, row_ptr + 1, 0, bits, c->stream));
+  SDGP_HIP(hipcub::DeviceSegmentedRadixSort::SortPairs(nullptr, tb, col2, col, val2, val, (int)k.nnz, (int)nr, begin,
+                                                       end, 0, bits, c->stream));
   tmp = c->get<char>(S_SORT_TMP, tb);
-  SDGP_HIP(hipcub::DeviceSegmentedRadixSort::SortPairs(tmp, tb, col2, col, val2, val, (int)k.nnz, (int)n,
-                                                       row_ptr, row_ptr + 1, 0, bits, c->stream));
+  SDGP_HIP(hipcub::DeviceSegmentedRadixSort::SortPairs(tmp, tb, col2, col, val2, val, (int)k.nnz, (int)nr, begin, end, 0,
+                                                       bits, c->stream));
 }
 
 }  // namespace sdgp

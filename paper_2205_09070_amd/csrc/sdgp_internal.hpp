@@ -89,7 +89,7 @@ bool tune_cache_put(const std::string& path, const std::string& key, const TuneC
 enum Slot {
   S_KEYS, S_KEYS_ALT, S_IDX, S_PERM, S_XS, S_YS, S_CELL_START, S_BBOX,
   S_F, S_M, S_BP, S_CELLMASK, S_RUN_CNT, S_RUN_POS, S_RUN_PTR, S_RUNS, S_IV_CNT, S_IV_PTR, S_IV,
-  S_ROW_NNZ, S_ROW_PTR, S_COL, S_VAL, S_SORT_TMP, S_COL2, S_VAL2, S_ROWLEN2,
+  S_ROW_NNZ, S_ROW_PTR, S_COL, S_VAL, S_SORT_TMP, S_COL2, S_VAL2, S_ROWLEN2, S_CANON_ROWS, S_CANON_SEG,
   S_CG_X, S_CG_R, S_CG_P, S_CG_Q, S_CG_SCAL, S_CG_PART, S_CG_HIST_A, S_CG_HIST_B,
   S_CG_STATE, S_ZBITS, S_SLQ_WORK, S_SLQ_OUT, S_ADJ_ROW, S_ADJ_G, S_ADJ_PART,
   S_RED_PART, S_RED_OUT, S_X0S, S_MISC, S_POST, S_COUNTER, S_MASK_CNT, S_MASK_PTR, S_MASK,
@@ -261,6 +261,13 @@ struct CsrOut {
   double* val;
   int64_t capacity;
 };
+// What the canonical order needs of the count: row lengths by caller index, and
+// the rows too long for the rank sort (sorted positions).
+struct CanonRows {
+  int64_t* len = nullptr;    // [n + 1]
+  int32_t* rows = nullptr;   // [n_long]
+  int64_t n_long = 0;
+};
 // Count + fill; the CSR lives in context buffers (S_ROW_PTR, S_COL, S_VAL),
 // or in the caller's arrays when out is given (then, when nnz exceeds
 // out->capacity, row_ptr is written and the fill is skipped: col / val of
@@ -269,7 +276,7 @@ struct CsrOut {
 Csr assemble_sorted(Ctx* c, const Sorted& s, const KParams& kp, const Bumps& b,
                     const int32_t* iv_ptr, const int2* iv, bool add_noise,
                     int64_t* candidates, PhaseTimer* t, bool core_only = false,
-                    const CsrOut* out = nullptr);
+                    const CsrOut* out = nullptr, CanonRows* canon = nullptr);
 // Population assembly: members m = 0..B-1 with hyperparameters h[m] on the
 // shared ordering s, every phase (bump values, cell masks, bump runs,
 // candidate intervals, count, scan, fill) one launch with the member as
@@ -284,8 +291,9 @@ struct PopAssembled {
 };
 std::vector<PopAssembled> assemble_population(Ctx* c, const Sorted& s, const sdgp_kernel_desc& d,
                                               const std::vector<const double*>& h, bool add_noise);
-// Canonical (caller order, ascending columns) copy of a sorted-order CSR.
-void canonicalize(Ctx* c, const Sorted& s, const Csr& k, int64_t* row_ptr,
+// Canonical (caller order, ascending columns) copy of a sorted-order CSR that was
+// assembled with canon.
+void canonicalize(Ctx* c, const Sorted& s, const Csr& k, const CanonRows& canon, int64_t* row_ptr,
                   int32_t* col, double* val);
 // Cross-covariance kappa between test points (rows, caller order) and the
 // sorted training points (columns) as CSR, and the prior variances

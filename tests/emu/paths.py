@@ -5,6 +5,7 @@ child process started with emu_env():
 """
 from __future__ import annotations
 
+import ctypes as C
 import os
 import re
 import sys
@@ -211,6 +212,39 @@ def case_sides(lib):
     for m in (0, 2):                        # the largest core radius: the single call's order
         v1, g1, _ = c.lml_grad(w.desc, w.x, w.y, H[m], est)
         assert v[m] == v1 and (g[m] == g1).all()
+
+
+def case_canonical(lib):
+    """Caller-order CSR with rows past the rank sort's 512 entries.  Up to a
+    quarter of them: the short rows are ranked and the segmented sort sees the
+    long ones alone; more: all rows are sorted.  Either way the result is the
+    sorted-order assembly in the caller's order."""
+    k = 530                                 # a clique of points under one bump
+    for n in (4 * k + 3, 4 * k, 4 * k - 1):
+        rng = np.random.default_rng(5)
+        x = 0.6 + 0.4 * rng.random((n, 2))
+        x[rng.permutation(n)[:k]] = 0.25 + 0.01 * rng.random((k, 2))
+        d = wl.KernelDesc(2, 1, 1, 0, 1)
+        h = wl.pack_hyper(d, 1.0, 0.03, np.full((1, 1), 0.7), np.ones((1, 1)), np.full((1, 1), 0.05),
+                          np.full((1, 1, 2), 0.255), 1e-2)
+        c = EmuContext(lib)
+        nnz = c.kernel_nnz(d, x, h)
+        srp, scol, sval, perm = c.kernel_assemble_sorted(d, x, h, nnz)
+        rp, col, val = np.zeros(n + 1, dtype=np.int64), np.zeros(nnz, dtype=np.int32), np.zeros(nnz)
+        out, dd = _lib.I64(0), _lib.desc_of(d)
+        lines = _traced(lambda: c._check(c.lib.sdgp_kernel_assemble(
+            c.h, C.byref(dd), x.ctypes.data, n, h.ctypes.data, 1, rp.ctypes.data, col.ctypes.data, val.ctypes.data,
+            nnz, C.byref(out))))
+        rows = perm[np.repeat(np.arange(n), np.diff(srp))]
+        order = np.lexsort((perm[scol], rows))
+        assert out.value == nnz and (np.diff(rp) > 512).sum() == k
+        assert (rp[1:] == np.cumsum(np.bincount(rows, minlength=n))).all() and rp[0] == 0
+        assert (col == perm[scol][order]).all() and (val == sval[order]).all()
+        grids = {ln[0]: ln[1] for ln in lines if ln[0].startswith("k_canon")}
+        print("canonical %d rows, %d long: %s" % (n, k, grids))
+        split = n >= 4 * k
+        assert grids.get("k_canon_rank") == ((n + 3) // 4 if split else None)
+        assert grids["k_canon_copy"] == ((k if split else n) + 3) // 4
 
 
 if __name__ == "__main__":
