@@ -247,6 +247,42 @@ def case_canonical(lib):
         assert grids["k_canon_copy"] == ((k if split else n) + 3) // 4
 
 
+def case_block_members(lib):
+    """The block CG over several members that stop at different iterations, over
+    CSR rows and over union lists (with few update blocks: with tile flags),
+    against single solves and with its iterations replayed from a graph; and the
+    replay of a solve whose y goes alone."""
+    w = small(n=400)
+    p = wl.unpack_hyper(w.desc, w.h)
+    H = np.array([wl.pack_hyper(w.desc, s2, f * p["r_core"], p["a"], p["beta"], p["r"], p["c"], noise)
+                  for s2, f, noise in ((1.0, 1.0, 3e-2), (0.3, 0.7, 3.0), (2.0, 0.8, 3e-1))])
+    for opts in ({"union_spmm": 0}, {"union_spmm": 1, "update_blocks": 4}):
+        c = EmuContext(lib)
+        for k, v in opts.items():
+            c.set_option(k, v)
+        est = _lib.estimator(probes=3, seed=3, cg_rtol=1e-6, cg_max_iter=900, precond=1)
+        v, g, st, info = c.lml_grad_batched(w.desc, w.x, w.y, H, est)
+        assert (st == 0).all() and c.get_option("last_update_blocks") > 0
+        iters = [i.cg_iters for i in info]
+        c.set_option("graph", 1)
+        vg, gg, st, info = c.lml_grad_batched(w.desc, w.x, w.y, H, est)
+        print("%s: iterations %s" % (opts, iters))
+        assert len(set(iters)) == 3 and iters == [i.cg_iters for i in info]
+        assert (v == vg).all() and (g == gg).all()
+        c.set_option("graph", 0)
+        for m in range(3):
+            v1, g1, _ = c.lml_grad(w.desc, w.x, w.y, H[m], est)
+            assert m > 0 or (v[m] == v1 and (g[m] == g1).all())
+            assert abs(v[m] - v1) <= 1e-5 * abs(v1) and np.abs(g[m] - g1).max() <= 1e-4 * np.abs(g1).max()
+        est = _lib.estimator(probes=3, seed=3, cg_rtol=1e-6, probe_rtol=3e-1, cg_max_iter=900, precond=1)
+        v, g, _ = c.lml_grad(w.desc, w.x, w.y, H[0], est)
+        alone = c.get_option("last_y_tail")
+        c.set_option("graph", 1)
+        vg, gg, _ = c.lml_grad(w.desc, w.x, w.y, H[0], est)
+        print("  alone %d iterations" % alone)
+        assert alone > 0 and alone == c.get_option("last_y_tail") and v == vg and (g == gg).all()
+
+
 if __name__ == "__main__":
     globals()["case_" + sys.argv[2]](sys.argv[1])
     print("case %s holds" % sys.argv[2], flush=True)
