@@ -72,8 +72,8 @@ struct RowSweep {
   }
 };
 
-// Plain SpMM of 35 columns and more that do not make whole 16-byte pairs: Y = A X
-// (one wave per row, lanes over a 64-column chunk).
+// Plain SpMM of columns that do not make whole 16-byte pairs, 35 and more of them or
+// few rows: Y = A X (one wave per row, lanes over a 64-column chunk).
 __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t* __restrict__ row_ptr,
                                               const int32_t* __restrict__ col, const double* __restrict__ val,
                                               const double* __restrict__ X, int R, double* __restrict__ Y) {
@@ -430,8 +430,12 @@ void spmm(Ctx* c, const Csr& A, const double* X, int R, double* Y) {
   // order 3 / 17 / 25 / 33 columns 0.44 / 0.47 / 0.56 / 0.66 -> 0.26 / 0.43 / 0.55
   // / 0.67).  Two slabs of unaligned pairs lose to k_spmm's one chunk of 64 in
   // random order, where the gathers come from HBM (49 columns 1.23 against 0.87).
+  // Few rows leave the GPU idle with four of them to a wavefront, and a long row is
+  // a chain four times as long as with a wavefront to itself: 31 columns, rows of
+  // 1000 entries, slabs against k_spmm 74 / 36 us at 1000 rows, 74 / 63 at 2000, 92
+  // / 119 at 4000 (256 entries: 21 / 11, 21 / 18, 21 / 32); so up to 12 rows a CU.
   const bool pairs = R % 2 == 0 && (reinterpret_cast<uintptr_t>(X) % 16) == 0 && (reinterpret_cast<uintptr_t>(Y) % 16) == 0;
-  if (pairs || (R <= 33 && A.n <= 0x7fffffffLL)) {
+  if (pairs || (R <= 33 && A.n > 12 * cu && A.n <= 0x7fffffffLL)) {
     spmm_slab(c, A, X, R, Y, pairs);
     return;
   }
