@@ -52,6 +52,7 @@ constexpr int kSlab = 32;        // columns per slab
 constexpr int kSC = kSlab + 1;   // LDS stride of per-column values (slab columns + column 0)
 constexpr int kMaxNbs = 32768;   // SpMM blocks
 constexpr int kMaxNbu = 8192;    // upper bound on the update kernels' grid (default: one resident round)
+constexpr int kFlagBumps = 8;    // tile flags of F from more bump functions on (twice that: assembled operator)
 constexpr int kGS = 2;           // row-steps whose loads the update passes issue together
 constexpr int64_t kUnionMinRows = 65536;  // union-list SpMM by default from this many rows
 constexpr int64_t kUnionCheckRows = (int64_t)1 << 25;  // from here 16 rows could hold 2^29 entries
@@ -969,7 +970,7 @@ __device__ void put_yfold_partials(const CgArgs& A, double* red, bool has0, doub
 
 // Tiles of 16 rows without bump values.  A bump function covers a small part of
 // the points (about 2% at 64 balls of radius 0.03 - 0.06 in the unit cube), so
-// most tiles of F are zero (sweep_tiles).  Bound by one read of F, once a
+// most tiles of F are zero (Sweep).  Bound by one read of F, once a
 // solve; one wavefront per tile.
 __global__ __launch_bounds__(kT) void k_cg_ftiles(const CgArgs* __restrict__ AA, uint8_t* __restrict__ fz, int64_t ld) {
   const CgArgs& A = AA[blockIdx.z];
@@ -1007,7 +1008,12 @@ __device__ __forceinline__ int64_t wave_base(const CgArgs& A, int64_t k) {
 // -> FW 2: 1.19 -> 1.06 ms (10^6 points in 4-D, 32 bumps), 0.411 -> 0.407 ms
 // (4 10^5 points in 3-D, 16).  With one tile per wavefront the flag's load only
 // delays the tile's own (2 10^4 points: 60 -> 63 us), so FW 2 is taken from two
-// tiles on.
+// tiles on, and only where F is wide enough for what it saves (over CSR rows in
+// 3-D, us, factored and assembled operator, which reads F once a pass where
+// the other reads it twice): 3 bumps 218 -> 220 and 221 -> 230 (2 10^5 points, 4 probes),
+// 1067 -> 1085 (10^6, 32 probes); 8 bumps 221 -> 223 and 253 -> 262, 1086 -> 1099;
+// 16 bumps 237 -> 230 and 271 -> 274, 1137 -> 1122; 32 bumps 280 -> 251 and 354 ->
+// 342, 1332 -> 1178.
 template <int FW>
 struct Sweep {
   int64_t k = 0;        // FW 1: the next step; FW 2: the step after the 64 of m
@@ -1782,14 +1788,15 @@ void launch_iteration(hipStream_t st, const CgArgs* dA, const Launch& L, Ctx* c)
   }
   k_cg_colsum<<<dim3(L.ns == 0 ? 1 : L.R, 1, L.B), kSumT, 0, st>>>(dA, 0);   // (column 0 alone: its partials only)
   SDGP_CHECK_LAUNCH();
-  if (L.fz) k_cg_update_xr<NI, 2><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
+  constexpr int kFz = NI > kFlagBumps ? 2 : 1;    // (no flags below)
+  if (L.fz) k_cg_update_xr<NI, kFz><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else if (L.fw) k_cg_update_xr<NI, 1><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else k_cg_update_xr<NI, 0><<<dim3(L.nbu, L.ns + 1, L.B), kT, 0, st>>>(dA);
   SDGP_CHECK_LAUNCH();
   if (L.use_pc) k_cg_coef<<<dim3(L.R, 1, L.B), kSumT, 0, st>>>(dA);
   else k_cg_colsum<<<dim3(L.R, 1, L.B), kSumT, 0, st>>>(dA, 1);
   SDGP_CHECK_LAUNCH();
-  if (L.fz) k_cg_update_p<NI, 2><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
+  if (L.fz) k_cg_update_p<NI, kFz><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else if (L.fw) k_cg_update_p<NI, 1><<<dim3(L.nbu, L.ns, L.B), kT, 0, st>>>(dA);
   else k_cg_update_p<NI, 0><<<dim3(L.nbu, L.ns + 1, L.B), kT, 0, st>>>(dA);
   SDGP_CHECK_LAUNCH();
@@ -2226,8 +2233,9 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
   const bool tail_ok = B == 1 && ns > 0 && probe_cols && prt > rtol && !c->in_trial;
   double* s_part = c->get<double>(S_CG_PART, std::max((size_t)R * nbs * B, tail_ok ? (size_t)nbs_y : 0));
   const int64_t nft = (n + 15) / 16;             // 16-row tiles of F
-  // tile flags pay from two tiles per wavefront on (sweep_tiles)
-  uint8_t* fz = fw && n > (int64_t)nbu * kBlockRows ? c->get<uint8_t>(S_CG_FTILES, (size_t)nft * B) : nullptr;
+  // tile flags pay from two tiles per wavefront and from about a line of F a row on (Sweep)
+  const bool use_flags = fw && n > (int64_t)nbu * kBlockRows && n1 > (use_lr ? kFlagBumps : 2 * kFlagBumps);
+  uint8_t* fz = use_flags ? c->get<uint8_t>(S_CG_FTILES, (size_t)nft * B) : nullptr;
   std::vector<CgArgs> hA(B);
   for (int m = 0; m < B; ++m) {
     CgArgs& A = hA[m];

@@ -303,6 +303,19 @@ def case_few_rows(lib):
         assert (np.abs(Y - S @ X) <= 1e-14 * (abs(S) @ np.abs(X))).all()
 
 
+def case_tile_flags(lib):
+    """Tiles of F without bump values are flagged where F is wide: past 8 bump
+    functions with the factored operator, past 16 with the assembled one."""
+    est = lambda op: _lib.estimator(probes=1, seed=3, cg_rtol=1e-1, cg_max_iter=50, precond=1, operator_form=op)
+    for n1, op, flags in ((8, 1, False), (9, 1, True), (16, 0, False), (17, 0, True)):
+        w = small(n=70, n1=n1)
+        c = EmuContext(lib)
+        c.set_option("update_blocks", 1)
+        names = {ln[0] for ln in _traced(lambda: c.lml_grad(w.desc, w.x, w.y, w.h, est(op)))}
+        print(n1, op, "k_cg_ftiles" in names)
+        assert ("k_cg_ftiles" in names) == flags
+
+
 if __name__ == "__main__":
     globals()["case_" + sys.argv[2]](sys.argv[1])
     print("case %s holds" % sys.argv[2], flush=True)

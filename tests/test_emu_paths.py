@@ -21,7 +21,7 @@ def emu_lib(tmp_path_factory):
     shutil.rmtree(lib + ".src", ignore_errors=True)
 
 
-@pytest.mark.parametrize("case", ["timing", "cap", "cap_lists", "refused_trial", "csr_grid", "sides", "canonical", "block_members", "few_rows"])
+@pytest.mark.parametrize("case", ["timing", "cap", "cap_lists", "refused_trial", "csr_grid", "sides", "canonical", "block_members", "few_rows", "tile_flags"])
 def test_path(emu_lib, case, tmp_path):
     from tests.emu import emu_ctx
     r = subprocess.run([sys.executable, "-u", os.path.join(ROOT, "tests", "emu", "paths.py"), emu_lib, case],
