@@ -516,6 +516,10 @@ __device__ __forceinline__ void union_mma(const dv2* xv, double yv, const double
 // kept (ms at 400,000 points): the next batch's columns loaded a batch ahead
 // 0.196 against 0.188; batches of 32 columns at 4 / 5 / 6 wavefronts per SIMD
 // 0.203 / 0.202 / 0.215 against 0.185; values loaded one by one 0.188.
+// Where the rows share a bump (1,640 dense columns: 1024 values a batch) a batch's
+// values beyond the first 384 were loaded one by one, ten round trips in a row, and
+// those few groups set the launch's time: 128,594 points in 2-D, 6 such balls,
+// 0.219 ms; by whole rounds of 384 ahead of the gathers 0.183.
 // kWide: slabs of 4 GiB and more (64-bit row offsets).  kMode 1: slab 0 and
 // column 0 (grid y = 1); kMode 2: slabs 1.. (grid y = ns - 1); kMode 3: a
 // Taylor term over all slabs (grid y = ns), Q = P - A P / alpha (1 / alpha in
@@ -529,7 +533,7 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
   constexpr bool kTaylor = kMode == 3;
   if (!kTaylor && stopped(A)) return;
   constexpr bool kY = kMode == 1;
-  constexpr int kVL = 3;                          // values per lane loaded ahead (384 of a batch's at most 1024)
+  constexpr int kVL = 3;                          // pairs of values per lane loaded at a time (384 of a batch's at most 1024)
   __shared__ __align__(16) double tile[kT / kWave][kBE * kGR + 2];   // (+ the unused places' target)
   const GL int64_t* gv = (const GL int64_t*)A.gv;
   const GL int32_t* glen = (const GL int32_t*)A.glen;
@@ -552,6 +556,20 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
   const int64_t bi = blockIdx.x >> 3, nbx = gridDim.x >> 3;
   const int64_t nx = (((n + 7) >> 3) + kGR - 1) & ~(int64_t)(kGR - 1), lo = xcd * nx, hi = min(n, lo + nx);
   const auto seq = std::make_integer_sequence<int, 4>{};
+  auto clear = [&]() {
+    __builtin_amdgcn_wave_barrier();              // the last batch's tile is read
+#pragma unroll
+    for (int m = 0; m < kBE / 8; ++m) *reinterpret_cast<dv2*>(tw + 2 * (lane + kWave * m)) = dv2{0.0, 0.0};
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto put = [&](uint32_t i, uint32_t e, const dv2* v, const uint32_t* at2) {
+#pragma unroll
+    for (int m = 0; m < kVL; ++m) {
+      const uint32_t k = i + 2 * (lane + kWave * m);
+      if (k < e) tw[at2[m] & 0xffff] = v[m].x;
+      if (k + 1 < e) tw[at2[m] >> 16] = v[m].y;
+    }
+  };
   double pq0 = 0.0, pq1 = 0.0, pqy = 0.0;
   for (int64_t pb = lo + bi * kUTile + w * kGR; pb < hi; pb += nbx * kUTile) {
     const int64_t q = pb >> 4;
@@ -563,6 +581,19 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
     const uint32_t a0 = (uint32_t)(G.sched ? G.sched[pb] : (int32_t)pb);
     double acc[4][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
     double accy = 0.0;
+    // values i .. e - 1 with their places, in pairs (aligned: batches begin at multiples of 4)
+    auto fetch = [&](uint32_t i, uint32_t e, dv2* v, uint32_t* at2) {
+#pragma unroll
+      for (int m = 0; m < kVL; ++m) {
+        const uint32_t k = i + 2 * (lane + kWave * m);
+        v[m] = dv2{0.0, 0.0};
+        at2[m] = 0u;
+        if (k < e) {
+          v[m] = *(const GL dv2*)(vlb + k * 8u);
+          at2[m] = *(const GL uint32_t*)(pob + k * 2u);
+        }
+      }
+    };
     uint32_t vb = 0;
     for (int e0 = 0; e0 < len; e0 += kBE) {       // uniform over the wavefront
       const int rem = len - e0;
@@ -573,15 +604,14 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
       const uint32_t cj = ei < min(rem, kBE) ? *(const GL uint32_t*)(cb + (uint32_t)(e0 + ei) * 4u) : a0;
       dv2 vv[kVL];
       uint32_t pp[kVL];
-#pragma unroll
-      for (int m = 0; m < kVL; ++m) {             // pairs of values (aligned: batches begin at multiples of 4)
-        const uint32_t i = vb + 2 * (lane + kWave * m);
-        vv[m] = dv2{0.0, 0.0};
-        pp[m] = 0u;
-        if (i < ve) {
-          vv[m] = *(const GL dv2*)(vlb + i * 8u);
-          pp[m] = *(const GL uint32_t*)(pob + i * 2u);
-        }
+      uint32_t i0 = vb;                           // (uniform)
+      fetch(i0, ve, vv, pp);
+      clear();
+#pragma unroll 1
+      while (ve - i0 > 2 * kWave * kVL) {         // a batch of many values: all but the last of them ahead of the gathers
+        put(i0, ve, vv, pp);
+        i0 += 2 * kWave * kVL;
+        fetch(i0, ve, vv, pp);
       }
       const double yv = kY ? G.P[cj] : 0.0;
       const uint32_t off = kWide ? cj : cj * (kSlab * 8);
@@ -590,18 +620,7 @@ __global__ __launch_bounds__(kT, kUnionPerCu) void k_cg_spmm_u(const CgArgs* __r
       union_load<kWide, 0>(off, Pb, (uint32_t)(16 * j), xv, seq);
       if (nc > 1) union_load<kWide, 1>(off, Pb, (uint32_t)(16 * j), xv, seq);
       if (nc > 2) union_load<kWide, 2>(off, Pb, (uint32_t)(16 * j), xv, seq);
-      __builtin_amdgcn_wave_barrier();            // the last batch's tile is read
-#pragma unroll
-      for (int m = 0; m < kBE / 8; ++m) *reinterpret_cast<dv2*>(tw + 2 * (lane + kWave * m)) = dv2{0.0, 0.0};
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int m = 0; m < kVL; ++m) {
-        const uint32_t i = vb + 2 * (lane + kWave * m);
-        if (i < ve) tw[pp[m] & 0xffff] = vv[m].x;
-        if (i + 1 < ve) tw[pp[m] >> 16] = vv[m].y;
-      }
-      for (uint32_t i = vb + 2 * kWave * kVL + lane; i < ve; i += kWave)
-        tw[*(const GL uint16_t*)(pob + i * 2u)] = *(const GL double*)(vlb + i * 8u);
+      put(i0, ve, vv, pp);
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_s_setprio(1);              // a wavefront with its operands at hand goes first
       union_mma<kY, 0>(xv, yv, at, aty, acc, accy, seq);
