@@ -1332,11 +1332,6 @@ __global__ __launch_bounds__(kBlock) void k_canon_rank(const int64_t* __restrict
   }
 }
 
-__global__ void k_iota_i64(int64_t* p, int64_t n) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
 }  // namespace
 
 // =========================================================== host side

@@ -54,7 +54,14 @@ constexpr int kMaxNbs = 32768;   // SpMM blocks
 constexpr int kMaxNbu = 8192;    // upper bound on the update kernels' grid (default: one resident round)
 constexpr int kFlagBumps = 8;    // tile flags of F from more bump functions on (twice that: assembled operator)
 constexpr int kGS = 2;           // row-steps whose loads the update passes issue together
-constexpr int64_t kUnionMinRows = 65536;  // union-list SpMM by default from this many rows
+// Union-list SpMM by default from this many rows, the line from which the tuner
+// times both forms on the caller's problem (kTuneMinRows).  Without it the lists win
+// already from about 20,000 rows: a whole evaluation with 32 probes and 8 bumps in
+// 3-D, CSR rows / lists, 30 entries per row 18.4 / 19.3 ms at 10,500 points (407
+// iterations), 30.8 / 30.5 at 20,000 (549), 36.0 / 32.9 at 30,000, 68.9 / 58.0 at
+// 65,000; 60 per row 31.8 / 33.7, 55.9 / 54.1, 66.6 / 59.3, 131 / 104; 16 members of
+// 20,000 points 122 / 104.
+constexpr int64_t kUnionMinRows = 65536;
 constexpr int64_t kUnionCheckRows = (int64_t)1 << 25;  // from here 16 rows could hold 2^29 entries
 
 struct CgState {
@@ -914,25 +921,7 @@ __device__ void put_y_partials(const CgArgs& A, double* red, bool has0, double v
 //   B[k][c] = w[4 s + k][2 c + par]  (lane 16 k + c; w in LDS, stride kSlab),
 // so D[4 q + g][j] (lane (g, j), register q) is the product for the row the
 // lane owns at step q, even column (de) / odd column (dd).
-template <int NS>
-__device__ __forceinline__ void fw_tile(const GL double* __restrict__ F, int n1, int64_t n, int64_t base,
-                                        const double* w, d4& de, d4& dd) {
-  const int g = lane_id() >> 4, j = lane_id() & 15;
-  const int64_t row = base + j;
-  de = d4{0.0, 0.0, 0.0, 0.0};
-  dd = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const int i = 4 * s + g;
-    const bool ok = i < n1;
-    const double fa = (row < n && ok) ? F[row * n1 + i] : 0.0;
-    const double b0 = ok ? w[i * kSC + 2 * j] : 0.0;
-    const double b1 = ok ? w[i * kSC + 2 * j + 1] : 0.0;
-    de = __builtin_amdgcn_mfma_f64_16x16x4f64(fa, b0, de, 0, 0, 0);
-    dd = __builtin_amdgcn_mfma_f64_16x16x4f64(fa, b1, dd, 0, 0, 0);
-  }
-}
-// fw_tile plus, when yfold, the column-0 product in lanes j == 0:
+// With yfold also the column-0 product in lanes j == 0:
 // dy[q] of lane (g, 0) = sum_i F[base + 4q + g][i] w[i][kSlab].
 template <int NS>
 __device__ __forceinline__ void fw_tile_y(const GL double* __restrict__ F, int n1, int64_t n, int64_t base,
@@ -2195,8 +2184,7 @@ std::vector<CgResult> block_cg_multi(Ctx* c, const std::vector<CgMember>& mem, c
       }
     }
   }
-  // Union lists of the shared-gather SpMM (automatic from kUnionMinRows rows:
-  // below that, building the lists costs more than the solve saves)
+  // Union lists of the shared-gather SpMM (automatic from kUnionMinRows rows on)
   bool uni = ns > 0 && (sh.union_spmm > 0 || (sh.union_spmm < 0 && n >= kUnionMinRows));
   // The SpMM grid over CSR rows.  A tuned grid belongs to the form that it was
   // tuned with: lists that do not fit leave theirs, and so does column 0 when it

@@ -65,9 +65,10 @@ struct Grid {
 struct Ctx;
 
 // Launch shape of the block CG (the autotuner's search space).  0 / -1 mean
-// "the library default": spmm_blocks 0 = 32768 blocks, update_blocks 0 = one
-// resident round of the update kernels, union_spmm -1 = union lists from
-// 65536 rows, fw_mfma -1 = matrix-core F w products.
+// "the library default": spmm_blocks 0 = one resident round over union lists,
+// 32768 blocks over CSR rows; update_blocks 0 = one resident round of the update
+// kernels; union_spmm -1 = union lists from 65536 rows; fw_mfma -1 = matrix-core
+// F w products.
 struct TuneChoice {
   int spmm_blocks = 0;
   int update_blocks = 0;

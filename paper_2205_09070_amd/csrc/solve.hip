@@ -739,15 +739,16 @@ __global__ __launch_bounds__(kSlqT) void k_slq(const double* __restrict__ ha, co
     iv[1] = iv[3] = ghi;
   }
   __syncthreads();
-  // first round: thread 0 of the lower half counts at 0 (some theta <= 0: no
-  // logarithm); then point i of a half at the (i + 1)/160 part of its interval
+  // point i of a half at the (i + 1)/160 part of its interval; the last of each
+  // half, whose point would be the interval's end, counts at 0 instead (some
+  // theta <= 0: no logarithm)
   for (int round = 0; round < 64; ++round) {
     const double a0 = iv[0], b0 = iv[1], a1 = iv[2], b1 = iv[3];
     const bool go = b0 - a0 > 1e-10 * b0 || b1 - a1 > 1e-10 * b1;
     if (!go && round > 0) break;
     const int half = t >= kSlqH ? 1 : 0, i = t - half * kSlqH;
     const double a = half ? a1 : a0, b = half ? b1 : b0;
-    const bool zero = i == kSlqH - 1;           // the last point of a half is the interval's end: 0 instead
+    const bool zero = i == kSlqH - 1;
     const double x = zero ? 0.0 : a + (b - a) * ((i + 1) / (double)kSlqH);
     __syncthreads();                            // iv is read
     if (t < 2) hit[t] = kSlqH;

@@ -6,7 +6,7 @@
 // calls -- in this process or another one -- start from it.  The store is a
 // small JSON object, one entry per line:
 //   {
-//   "gfx950|ni16|ns1|b1|n19|r12|lr1": {"spmm_blocks": 32768, "update_blocks": 768, "union_spmm": 1, "fw_mfma": 1, "ms_per_iter": 1.14, "default_ms_per_iter": 1.15},
+//   "gfx950|u16|ni16|ns1|b1|n19|r12|lr1|pc1": {"spmm_blocks": 2048, "update_blocks": 768, "union_spmm": 1, "fw_mfma": 1, "ms_per_iter": 0.85, "default_ms_per_iter": 0.86},
 //   ...
 //   }
 // Reading is tolerant: lines that do not parse are skipped, and a missing
