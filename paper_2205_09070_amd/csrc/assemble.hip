@@ -1667,7 +1667,7 @@ static Csr assemble_two_pass(Ctx* c, const Sorted& s, RowArgs A, int64_t* candid
   unsigned long long tot[3] = {0, 0, 0};
   if (canon) {
     canon->len = c->get<int64_t>(S_ROWLEN2, n + 1);
-    canon->rows = c->get<int32_t>(S_CANON_ROWS, n);
+    canon->rows = c->get<int32_t>(S_IDX, n);        // (free since the points are in order)
     k_canon_len<<<grid_for(n, kBlock), kBlock, 0, c->stream>>>(row_ptr, s.perm, n, canon->len, canon->rows, cand);
     SDGP_CHECK_LAUNCH();
     SDGP_HIP(hipMemcpyAsync(tot, cand, sizeof(tot), hipMemcpyDeviceToHost, c->stream));
@@ -1975,7 +1975,7 @@ void canonicalize(Ctx* c, const Sorted& s, const Csr& k, const CanonRows& cr, in
     SDGP_CHECK_LAUNCH();
   }
   if (nr == 0) return;
-  int64_t* seg = all ? nullptr : c->get<int64_t>(S_CANON_SEG, 2 * nr);
+  int64_t* seg = all ? nullptr : c->get<int64_t>(S_ROW_NNZ, 2 * nr);   // (at most n/2; the counts are summed)
   int32_t* col2 = c->get<int32_t>(S_COL2, k.nnz);
   double* val2 = c->get<double>(S_VAL2, k.nnz);
   k_canon_copy<<<grid_for(nr, kBlock / kWave), kBlock, 0, c->stream>>>(k.row_ptr, k.col, k.val, s.perm,

@@ -519,10 +519,12 @@ __device__ __forceinline__ void union_mma(const dv2* xv, double yv, const double
 // lists with a dense 4-value entry 1.0 KB per row, these 0.65 KB).  Per launch
 // with 33 columns, factored operator: 0.293 -> 0.180 ms at 400,000 points in
 // 3-D (60 entries per row), 0.695 -> 0.470 ms at 1,000,000 points in 4-D (50);
-// matrix cores 44% busy, LDS 25%, the texture data path 87%.  Measured and not
-// kept (ms at 400,000 points): the next batch's columns loaded a batch ahead
-// 0.196 against 0.188; batches of 32 columns at 4 / 5 / 6 wavefronts per SIMD
-// 0.203 / 0.202 / 0.215 against 0.185; values loaded one by one 0.188.
+// at 1,000,000 points in 3-D (0.433 ms) the texture data path is 93% busy, two
+// thirds of that waiting on the L1, the matrix cores 49%, LDS bank conflicts 15% of
+// the cycles.  Measured and not kept (ms at 400,000 points): the next batch's
+// columns loaded a batch ahead 0.196 against 0.188; batches of 32 columns at 4 / 5 /
+// 6 wavefronts per SIMD 0.203 / 0.202 / 0.215 against 0.185; values loaded one by
+// one 0.188.
 // Where the rows share a bump (1,640 dense columns: 1024 values a batch) a batch's
 // values beyond the first 384 were loaded one by one, ten round trips in a row, and
 // those few groups set the launch's time: 128,594 points in 2-D, 6 such balls,

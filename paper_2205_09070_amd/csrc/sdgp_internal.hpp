@@ -90,7 +90,7 @@ bool tune_cache_put(const std::string& path, const std::string& key, const TuneC
 enum Slot {
   S_KEYS, S_KEYS_ALT, S_IDX, S_PERM, S_XS, S_YS, S_CELL_START, S_BBOX,
   S_F, S_M, S_BP, S_CELLMASK, S_RUN_CNT, S_RUN_POS, S_RUN_PTR, S_RUNS, S_IV_CNT, S_IV_PTR, S_IV,
-  S_ROW_NNZ, S_ROW_PTR, S_COL, S_VAL, S_SORT_TMP, S_COL2, S_VAL2, S_ROWLEN2, S_CANON_ROWS, S_CANON_SEG,
+  S_ROW_NNZ, S_ROW_PTR, S_COL, S_VAL, S_SORT_TMP, S_COL2, S_VAL2, S_ROWLEN2,
   S_CG_X, S_CG_R, S_CG_P, S_CG_Q, S_CG_SCAL, S_CG_PART, S_CG_HIST_A, S_CG_HIST_B,
   S_CG_STATE, S_ZBITS, S_SLQ_WORK, S_SLQ_OUT, S_ADJ_ROW, S_ADJ_G, S_ADJ_PART,
   S_RED_PART, S_RED_OUT, S_X0S, S_MISC, S_POST, S_COUNTER, S_MASK_CNT, S_MASK_PTR, S_MASK,
