@@ -2637,8 +2637,8 @@ __device__ __forceinline__ void gather16_ragged(int cj, double vj, int rem, cons
   }
 }
 
-// (Xy null: no last column)
-__device__ __forceinline__ void ragged_row(int64_t k0, int64_t k1, const GL int32_t* __restrict__ col,
+// Entries k0 .. k1 - 1 of a row, 16 every step.  (Xy null: no last column)
+__device__ __forceinline__ void ragged_row(int64_t k0, int64_t k1, int step, const GL int32_t* __restrict__ col,
                                            const GL double* __restrict__ val, const GL double* __restrict__ Xs,
                                            int64_t ld, const GL double* __restrict__ Xy, dv2& q, double& y) {
   const int j = lane_id() & 15;
@@ -2647,10 +2647,10 @@ __device__ __forceinline__ void ragged_row(int64_t k0, int64_t k1, const GL int3
   bool in = k0 + j < k1;
   int cj = in ? col[k0 + j] : 0;
   double vj = in ? val[k0 + j] : 0.0;
-  for (int64_t kb = k0; __any(kb < k1); kb += 16) {
-    const bool inn = kb + 16 + j < k1;
-    const int cn = inn ? col[kb + 16 + j] : 0;
-    const double vn = inn ? val[kb + 16 + j] : 0.0;
+  for (int64_t kb = k0; __any(kb < k1); kb += step) {
+    const bool inn = kb + step + j < k1;
+    const int cn = inn ? col[kb + step + j] : 0;
+    const double vn = inn ? val[kb + step + j] : 0.0;
     if (Xy != nullptr && in) y += vj * Xy[(int64_t)(uint32_t)cj * ld];
     const int rem = (int)max((int64_t)0, min(k1 - kb, (int64_t)16));
     gather16_ragged(cj, vj, rem, Xs, ld, acc, std::make_integer_sequence<int, 16>{});
@@ -2663,7 +2663,20 @@ __device__ __forceinline__ void ragged_row(int64_t k0, int64_t k1, const GL int3
   y = row16_sum(y);
 }
 
-template <bool kPairs>
+// kForm: kPairs, kRagged, or kSpread: the same for up to 48 rows a CU, where rows of
+// very different lengths leave most of the GPU waiting for a few wavefronts (the rows
+// that share a bump are neighbours, so a wavefront's four rows are long together).
+// When one row of 64 evenly taken is more than twice as long as the average, a
+// wavefront takes rows far apart, and its four groups share them one after the other
+// where that is fewer steps.  33 columns, kRagged -> kSpread (wavefront per row): 141
+// entries per row with up to 1111 at 6500 points 71 -> 41 us (68), 313 with up to
+// 2136 158 -> 88 (122), 87 with up to 923 at 12,000 64 -> 38 (66); even rows 27.7 ->
+// 28.3 (8000 of 256).  Past that size spread rows lose the neighbours' common columns
+// in the L1: 73 entries at most, 80,000 points 54 -> 66 us.
+enum { kPairs, kRagged, kSpread };
+constexpr int kSpreadRows = 48;                   // rows a CU up to which kSpread is taken
+constexpr int kShare = 4;                         // steps that sharing the rows costs
+template <int kForm>
 __global__ __launch_bounds__(kT) void k_spmm_slab(int64_t n, const int64_t* __restrict__ row_ptr,
                                                   const int32_t* __restrict__ col, const double* __restrict__ val,
                                                   const double* __restrict__ X, int R, double* __restrict__ Y) {
@@ -2671,25 +2684,62 @@ __global__ __launch_bounds__(kT) void k_spmm_slab(int64_t n, const int64_t* __re
   const int Re = R & ~1;
   const int c0 = (int)blockIdx.y * kSlab + 2 * j;
   const int cc = c0 + 1 < Re ? c0 : Re - 2;   // lanes past the last column read a valid pair
-  const bool last = !kPairs && Re < R && blockIdx.y == 0;
+  const bool last = kForm != kPairs && Re < R && blockIdx.y == 0;
   const GL int32_t* cg = (const GL int32_t*)col;
   const GL double *vg = (const GL double*)val, *Xg = (const GL double*)X;
+  const GL double* Xy = last ? Xg + Re : nullptr;
   const int xcd = blockIdx.x & 7;
   const int64_t bi = blockIdx.x >> 3, nbx = gridDim.x >> 3;
   const int64_t nx = (n + 7) >> 3, lo = xcd * nx, hi = min(n, lo + nx);
-  for (int64_t pb = lo + bi * kTile + w * 4; pb < hi; pb += nbx * kTile) {
-    const int64_t a = pb + g;
+  auto put = [&](int64_t a, const dv2& q, double y) {
+    if (c0 + 1 < Re) {
+      if (kForm == kPairs) *reinterpret_cast<dv2*>(Y + a * R + c0) = q;
+      else *reinterpret_cast<dv2u*>(Y + a * R + c0) = q;
+    }
+    if (last && j == 0) Y[a * R + Re] = y;
+  };
+  // rows between a wavefront's groups, and between the wavefronts of a block
+  int64_t gs = 1, ws = 4;
+  if (kForm == kSpread) {
+    const int64_t r = lane * n / kWave;           // one row in n / 64: is any twice as long as the average?
+    if (ballot64((row_ptr[r + 1] - row_ptr[r]) * n > 2 * row_ptr[n])) {
+      gs = 4 * nbx;                               // (the same in every wavefront of the launch)
+      ws = 1;
+    }
+  }
+  for (int64_t pb = lo + bi * (4 * ws) + w * ws; pb < hi; pb += nbx * kTile) {
+    const int64_t a = pb + g * gs;
     const bool live = a < hi;
     const int64_t k0 = live ? row_ptr[a] : 0, k1 = live ? row_ptr[a + 1] : 0;
     dv2 q;
     double y = 0.0;
-    if (kPairs) slab_row<false>(k0, k1, live ? (int32_t)a : 0, cg, vg, Xg + cc, R, nullptr, q, y);
-    else ragged_row(k0, k1, cg, vg, Xg + cc, R, last ? Xg + Re : nullptr, q, y);
-    if (live && c0 + 1 < Re) {
-      if (kPairs) *reinterpret_cast<dv2*>(Y + a * R + c0) = q;
-      else *reinterpret_cast<dv2u*>(Y + a * R + c0) = q;
+    if (kForm == kSpread && ws == 1) {
+      int64_t most = (k1 - k0 + 15) >> 4, all = (k1 - k0 + 63) >> 6;   // steps of the longest row; of all four, shared
+#pragma unroll
+      for (int o = 16; o < 64; o <<= 1) {
+        most = max(most, (int64_t)__shfl_xor((long long)most, o, 64));
+        all += __shfl_xor((long long)all, o, 64);
+      }
+      if (all + kShare < most) {                  // (uniform) the four groups share one row after the other
+        for (int r = 0; r < 4; ++r) {
+          const int64_t ar = pb + r * gs;
+          if (ar >= hi) break;
+          const int64_t r0 = (int64_t)readlane_u64((uint64_t)k0, 16 * r), r1 = (int64_t)readlane_u64((uint64_t)k1, 16 * r);
+          ragged_row(r0 + 16 * g, r1, 64, cg, vg, Xg + cc, R, Xy, q, y);
+#pragma unroll
+          for (int o = 16; o < 64; o <<= 1) {
+            q.x += __shfl_xor(q.x, o, 64);
+            q.y += __shfl_xor(q.y, o, 64);
+            y += __shfl_xor(y, o, 64);
+          }
+          if (g == 0) put(ar, q, y);
+        }
+        continue;
+      }
     }
-    if (last && live && j == 0) Y[a * R + Re] = y;
+    if (kForm == kPairs) slab_row<false>(k0, k1, live ? (int32_t)a : 0, cg, vg, Xg + cc, R, nullptr, q, y);
+    else ragged_row(k0, k1, 16, cg, vg, Xg + cc, R, Xy, q, y);
+    if (live) put(a, q, y);
   }
 }
 }  // namespace
@@ -2700,8 +2750,13 @@ void spmm_slab(Ctx* c, const Csr& A, const double* X, int R, double* Y, bool pai
   const int64_t tiles = (A.n + kTile - 1) / kTile;
   const int nb = (int)std::min<int64_t>(kMaxNbs, round8(tiles));
   const int ns = (R / 2 * 2 + kSlab - 1) / kSlab;
-  if (pairs) k_spmm_slab<true><<<dim3(nb, ns), kT, 0, c->stream>>>(A.n, A.row_ptr, A.col, A.val, X, R, Y);
-  else k_spmm_slab<false><<<dim3(nb, ns), kT, 0, c->stream>>>(A.n, A.row_ptr, A.col, A.val, X, R, Y);
+  if (pairs) {
+    k_spmm_slab<kPairs><<<dim3(nb, ns), kT, 0, c->stream>>>(A.n, A.row_ptr, A.col, A.val, X, R, Y);
+  } else if (A.n <= (int64_t)kSpreadRows * c->cu_count) {
+    k_spmm_slab<kSpread><<<dim3(nb, ns), kT, 0, c->stream>>>(A.n, A.row_ptr, A.col, A.val, X, R, Y);
+  } else {
+    k_spmm_slab<kRagged><<<dim3(nb, ns), kT, 0, c->stream>>>(A.n, A.row_ptr, A.col, A.val, X, R, Y);
+  }
   SDGP_CHECK_LAUNCH();
 }
 

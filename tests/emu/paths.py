@@ -286,21 +286,25 @@ def case_block_members(lib):
 
 def case_few_rows(lib):
     """Products with an odd number of columns: a wavefront per row up to 12 rows a
-    CU (256 CUs), four rows to a wavefront past it; both give the product."""
+    CU (256 CUs), four rows to a wavefront past it, far apart and shared up to 48
+    where some rows are long; all give the product."""
     c = EmuContext(lib)
-    for n, kernel in ((12 * 256, "k_spmm"), (12 * 256 + 1, "k_spmm_slab<false>")):
-        rng = np.random.default_rng(n)
-        lens = rng.integers(0, 20, n)
-        rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
-        col = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lens]).astype(np.int32)
-        val, X = rng.standard_normal(len(col)), rng.standard_normal((n, 3))
-        Y = np.zeros_like(X)
-        lines = _traced(lambda: c._check(c.lib.sdgp_csr_spmm(c.h, n, rp.ctypes.data, col.ctypes.data, val.ctypes.data,
-                                                             X.ctypes.data, 3, Y.ctypes.data)))
-        print(n, lines)
-        assert [ln[0] for ln in lines] == [kernel]
-        S = ssp.csr_matrix((val, col, rp), shape=(n, n))
-        assert (np.abs(Y - S @ X) <= 1e-14 * (abs(S) @ np.abs(X))).all()
+    for n, kernel in ((12 * 256, "k_spmm"), (12 * 256 + 1, "k_spmm_slab<kSpread>"),
+                      (48 * 256, "k_spmm_slab<kSpread>"), (48 * 256 + 1, "k_spmm_slab<kRagged>")):
+        for longest in (20, 700):
+            rng = np.random.default_rng(n)
+            lens = rng.integers(0, 20, n)
+            lens[n // 3:n // 3 + n // 40] = longest
+            rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+            col = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lens]).astype(np.int32)
+            val, X = rng.standard_normal(len(col)), rng.standard_normal((n, 3))
+            Y = np.zeros_like(X)
+            lines = _traced(lambda: c._check(c.lib.sdgp_csr_spmm(c.h, n, rp.ctypes.data, col.ctypes.data,
+                                                                 val.ctypes.data, X.ctypes.data, 3, Y.ctypes.data)))
+            print(n, longest, lines)
+            assert [ln[0] for ln in lines] == [kernel]
+            S = ssp.csr_matrix((val, col, rp), shape=(n, n))
+            assert (np.abs(Y - S @ X) <= 2e-13 * (abs(S) @ np.abs(X))).all()
 
 
 def case_tile_flags(lib):
