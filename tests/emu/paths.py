@@ -71,7 +71,7 @@ def case_cap(lib):
     w, s = small(n=130), small(n=70, seed=12)
     least = _least_cap(lib, w, est)
     print("least cap %d" % least)
-    for f in (1.0, 1.2, 1.4, 1.7, 2.0, 3.0):
+    for f in (1.0, 1.4, 2.0, 3.0):
         cap = int(least * f)
         c = EmuContext(lib)
         c.set_option("workspace_cap", cap)
@@ -104,7 +104,7 @@ def case_cap_lists(lib):
     nnz = EmuContext(lib).kernel_nnz(w.desc, w.x, w.h)
     _store(lib, w, nnz, (8, 8, 1, 1))
     seen = set()
-    for k in range(12):
+    for k in range(0, 12, 2):
         c = EmuContext(lib)
         c.set_option("autotune", 2)
         c.set_option("workspace_cap", int(400000 * 1.08 ** k))
