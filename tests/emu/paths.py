@@ -253,10 +253,10 @@ def case_block_members(lib):
     CSR rows and over union lists (with few update blocks: with tile flags),
     against single solves and with its iterations replayed from a graph; and the
     replay of a solve whose y goes alone."""
-    w = small(n=400)
+    w = small(n=300)
     p = wl.unpack_hyper(w.desc, w.h)
     H = np.array([wl.pack_hyper(w.desc, s2, f * p["r_core"], p["a"], p["beta"], p["r"], p["c"], noise)
-                  for s2, f, noise in ((1.0, 1.0, 3e-2), (0.3, 0.7, 3.0), (2.0, 0.8, 3e-1))])
+                  for s2, f, noise in ((1.0, 1.0, 1e-1), (0.3, 0.7, 3.0), (2.0, 0.8, 1.0))])
     for opts in ({"union_spmm": 0}, {"union_spmm": 1, "update_blocks": 4}):
         c = EmuContext(lib)
         for k, v in opts.items():
